@@ -255,7 +255,9 @@ ExportFn select_export(int m, int n);
 FwdFn select_wide_fwd(int m, int n, bool relax, int q); // q: tau_mode (roi.hip)
 FwdFn select_wide_soft_only(int m, int n, int q);
 BwdFn select_wide_bwd(int m, int n, bool adam, int q);
-// Slots (four elements each) one block of the wide backward covers.
+// Slots (four elements each) one block of the wide forward (select_wide_fwd)
+// and of the wide backward covers.
+int64_t wide_fwd_block_slots(bool relax);
 int64_t wide_bwd_block_slots(int m);
 
 } // namespace roi

@@ -836,11 +836,13 @@ using namespace roi;
 namespace roi {
 namespace {
 
-// Blocks one piece of `ngroups` groups needs in a launch.
-int64_t blocks_for(int64_t ngroups, int m, bool fwd)
+// Blocks one piece of `ngroups` groups needs in a launch.  relax: the forward
+// evaluates the relaxation (m > 8: it takes one slot per lane).
+int64_t blocks_for(int64_t ngroups, int m, bool fwd, bool relax)
 {
     if (m > 8 || (m == 8 && !fwd)) // wide kernels: m / 4 slots per group
-        return ceil_div(ngroups * (m / 4), fwd ? (int64_t)kBlock : wide_bwd_block_slots(m));
+        return ceil_div(ngroups * (m / 4),
+                        fwd ? wide_fwd_block_slots(relax) : wide_bwd_block_slots(m));
     const int u = fwd ? (m == 4 ? kUnrollFwd<4> : kUnrollFwd<8>) : kBwdChunks;
     return ceil_div(ngroups, (int64_t)u * kLaneBlock);
 }
@@ -854,7 +856,7 @@ struct Launcher {
     Fn fn;
     int block;
     int m;
-    bool fwd;
+    bool fwd, relax;
     hipStream_t stream;
     const char* what;
     int64_t blocks = 0;
@@ -875,7 +877,7 @@ struct Launcher {
 
     int add(Piece pc)
     {
-        const int64_t nb = std::min(blocks_for(pc.ngroups, m, fwd), max_blocks());
+        const int64_t nb = std::min(blocks_for(pc.ngroups, m, fwd, relax), max_blocks());
         if (batch.count == kMaxPieces || blocks + nb > max_blocks())
             if (int st = flush()) return st;
         if (batch.count == 0)
@@ -906,6 +908,7 @@ int mask_fwd_run(const char* what, bool soft, const roi_fwd_tensor* t, int count
     L.block = m > 8 ? kBlock : kLaneBlock;
     L.m = m;
     L.fwd = true;
+    L.relax = soft || with_s == 1;
     L.stream = stream;
     L.what = what;
     L.batch.key_base = make_key(seed, step, 0);

@@ -83,25 +83,21 @@ __device__ __forceinline__ float min4(const float (&x)[4])
     return fminf(fminf(x[0], x[1]), fminf(x[2], x[3]));
 }
 
-// Hard top-n by a bitonic sort of the group (descending), entry i = 4 part + e
-// of the group at lane `part`, slot e.  Each key travels with its index.  An
-// entry beats another when its key is larger, or (kTies) equal with a lower
-// index: the order of the ranks, ties to the lower index.  Without kTies the
-// keys must be distinct for the result to mean anything (the caller checks).
-// A stage (kk, j) pairs entry i with i ^ j; the pair is ordered descending
-// when (i & kk) == 0 and ascending otherwise, the lower entry of a
-// descending pair keeping the entry that beats.  j = 1, 2 pair slots of one
-// lane; j >= 4 pairs lane part with lane part ^ (j / 4), each lane keeping
-// one side of its four pairs.  The network is log2(m) (log2(m) + 1) / 2
-// stages of 4 entries per lane, against m comparisons per entry for counting
-// ranks, and keeps few values live.
-template <bool kTies>
+// Hard top-n of keys that may tie, by a bitonic sort of the group
+// (descending), entry i = 4 part + e of the group at lane `part`, slot e.  Each
+// key travels with its index.  An entry beats another when its key is larger,
+// or equal with a lower index.  A stage (kk, j) pairs entry i with i ^ j; the
+// pair is ordered descending when (i & kk) == 0 and ascending otherwise, the
+// lower entry of a descending pair keeping the entry that beats.  j = 1, 2
+// pair slots of one lane; j >= 4 pairs lane part with lane part ^ (j / 4),
+// each lane keeping one side of its four pairs.  This is the fallback of
+// wide_top_packed, which orders almost every wave.
 __device__ __forceinline__ bool beats(float ka, int ia, float kb, int ib)
 {
-    return kTies ? (ka > kb || (ka == kb && ia < ib)) : ka > kb;
+    return ka > kb || (ka == kb && ia < ib);
 }
 
-template <int KK, int J, bool kTies>
+template <int KK, int J>
 __device__ __forceinline__ void bitonic_stage(float (&k)[4], int (&ix)[4], int part)
 {
     if constexpr (J < 4) {
@@ -111,7 +107,7 @@ __device__ __forceinline__ void bitonic_stage(float (&k)[4], int (&ix)[4], int p
             const int hi = lo | J;
             // direction of the pair: (i & KK) with i = 4 part + lo
             const bool desc = KK < 4 ? ((lo & KK) == 0) : ((part & (KK >> 2)) == 0);
-            const bool sw = beats<kTies>(k[hi], ix[hi], k[lo], ix[lo]) == desc;
+            const bool sw = beats(k[hi], ix[hi], k[lo], ix[lo]) == desc;
             const float kl = k[lo], kh = k[hi];
             const int il = ix[lo], ih = ix[hi];
             k[lo] = sw ? kh : kl;
@@ -128,57 +124,186 @@ __device__ __forceinline__ void bitonic_stage(float (&k)[4], int (&ix)[4], int p
         for (int e = 0; e < 4; ++e) {
             const float o = lane_xor<D>(k[e]);
             const int oi = __float_as_int(lane_xor<D>(__int_as_float(ix[e])));
-            const bool take = beats<kTies>(o, oi, k[e], ix[e]) == keep_max;
+            const bool take = beats(o, oi, k[e], ix[e]) == keep_max;
             k[e] = take ? o : k[e];
             ix[e] = take ? oi : ix[e];
         }
     }
 }
 
-template <int M, int KK, int J, bool kTies>
+template <int M, int KK, int J>
 __device__ __forceinline__ void bitonic_from(float (&k)[4], int (&ix)[4], int part)
 {
-    bitonic_stage<KK, J, kTies>(k, ix, part);
+    bitonic_stage<KK, J>(k, ix, part);
     if constexpr (J > 1)
-        bitonic_from<M, KK, J / 2, kTies>(k, ix, part);
+        bitonic_from<M, KK, J / 2>(k, ix, part);
     else if constexpr (KK < M)
-        bitonic_from<M, KK * 2, KK, kTies>(k, ix, part);
+        bitonic_from<M, KK * 2, KK>(k, ix, part);
 }
 
 // Sorts the group's keys (four per lane, kf) and sets keep[e] (is this lane's
 // entry e among the n that beat the others) and sidx[e] (the index within the
 // group of the entry at sorted position 4 part + e, i.e. of rank 4 part + e).
-// For the hardware-log keys (kTies false) it returns whether every two keys of
-// the group are further apart than the margin of their errors (noise.hpp):
-// then the order is the exact keys' order and no two tie, and checking the
-// m - 1 pairs adjacent in the sorted order covers every pair.  For exact keys
-// (kTies) ties go to the lower index and the return value is true.
-template <int L, int N, bool kTies>
-__device__ __forceinline__ bool wide_top(const float (&kf)[4], int part, bool (&keep)[4],
-                                         int (&sidx)[4])
+template <int L, int N>
+__device__ __forceinline__ void wide_top_ties(const float (&kf)[4], int part, bool (&keep)[4],
+                                              int (&sidx)[4])
 {
     constexpr int M = 4 * L;
     float k[4] = {kf[0], kf[1], kf[2], kf[3]};
 #pragma unroll
     for (int e = 0; e < 4; ++e) sidx[e] = 4 * part + e;
-    bitonic_from<M, 2, 1, kTies>(k, sidx, part);
+    bitonic_from<M, 2, 1>(k, sidx, part);
     const int lane = (int)(threadIdx.x & 63);
     // the entry of rank n - 1, held by lane (n - 1) / 4 of the group
     const int src = lane - part + (N - 1) / 4;
     const float kth = __shfl(k[(N - 1) % 4], src);
     const int ith = __shfl(sidx[(N - 1) % 4], src);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        keep[e] = kTies ? !beats<true>(kth, ith, kf[e], 4 * part + e) : kf[e] >= kth;
-    if constexpr (kTies) return true;
-    float big = fmaxf(fmaxf(fabsf(kf[0]), fabsf(kf[1])), fmaxf(fabsf(kf[2]), fabsf(kf[3])));
-    big = group_max<L>(big);
-    const float margin = __builtin_fmaf(big, 0x1p-20f, kFastPairMargin);
-    // adjacent sorted pairs: three in the lane, and the lane's last with the
-    // next lane's first (the group's last lane has no successor)
-    bool sep = (k[0] - k[1] > margin) & (k[1] - k[2] > margin) & (k[2] - k[3] > margin);
-    const float next = __shfl(k[0], part + 1 < L ? lane + 1 : lane);
-    sep &= (part + 1 == L) || (k[3] - next > margin);
+    for (int e = 0; e < 4; ++e) keep[e] = !beats(kth, ith, kf[e], 4 * part + e);
+}
+
+// The median of three: max(a, b) for c = INT32_MAX, min(a, b) for c =
+// INT32_MIN (one v_med3_i32).
+__device__ __forceinline__ int med3(int a, int b, int c)
+{
+    const int lo = a < b ? a : b, hi = a < b ? b : a;
+    const int m = hi < c ? hi : c;
+    return lo > m ? lo : m;
+}
+
+// One stage of the packed sort below: entry i is paired with i ^ X, the lower
+// entry keeping the larger key.  X < 4 pairs slots of a lane; a larger X pairs
+// lane part with part ^ (X / 4) and slot e with e ^ (X % 4), `bound` being
+// INT32_MAX in the lanes that hold the lower entries and INT32_MIN elsewhere.
+template <int X>
+__device__ __forceinline__ void packed_stage(int (&p)[4], int bound)
+{
+    if constexpr (X < 4) {
+#pragma unroll
+        for (int lo = 0; lo < 4; ++lo) {
+            if ((lo ^ X) < lo) continue;
+            const int a = p[lo], b = p[lo ^ X];
+            p[lo] = a > b ? a : b;
+            p[lo ^ X] = a > b ? b : a;
+        }
+    } else {
+        int o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            o[e] = __float_as_int(lane_xor<X / 4>(__int_as_float(p[e ^ (X % 4)])));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = med3(p[e], o[e], bound);
+    }
+}
+
+// Float bits to integers of the same order (and back: the map is its own
+// inverse): the magnitude bits of a negative number are complemented.
+__device__ __forceinline__ int sortable_int(float f)
+{
+    const uint32_t u = __float_as_uint(f);
+    // a ^ (b & c)
+    return (int)__builtin_amdgcn_bitop3_b32(u, (uint32_t)((int32_t)u >> 31), 0x7FFFFFFFu, 0x78);
+}
+
+__device__ __forceinline__ float float_of_sortable_int(int v)
+{
+    return __int_as_float(sortable_int(__int_as_float(v)));
+}
+
+// Hard top-n by a bitonic sort of one 32-bit integer per key: the key's
+// order-preserving integer with its low log2(m) bits replaced by the entry's
+// index, so that an exchange is a minimum and a maximum (in a lane) or a DPP
+// move and a median (across lanes), and the index travels for free.  Every
+// merge of KK entries starts by pairing i with i ^ (KK - 1), after which all
+// comparisons point the same way and every lane exchange is one DPP
+// permutation (xor 1, 2, 3 or 7).  On MI355X the minimum, maximum, median and
+// DPP each issue in 4.2 cycles per wave: 16:32 over 1.31e9 weights sorts with
+// 350 issue cycles per wave instead of 940 with keys and indices carried
+// apart.
+//
+// Replacing the low bits moves a key by less than m ulps, m 2^-23 |K|.  The
+// result is decided -- the order of ranks 0 .. n-1 and the kept set are those
+// of the unpacked keys' exact counterparts -- when each of those ranks is
+// further from the next rank than the error of two keys:
+//   kExact: the keys are the exact ones, and packing is monotone, so the
+//     packed keys only have to differ above the index bits;
+//   else: hardware-log keys, kFastPairMargin + 2^-20 |K| (noise.hpp) plus the
+//     packing's m 2^-23 |K|, |K| the larger of the pair.
+// Ranks past n need no order among themselves.  Returns whether this lane's
+// ranks are decided (a group is when all its lanes are); a NaN anywhere in the
+// group, equal exact keys and an infinite hardware-log key among the checked
+// ranks are not.
+template <int L, int N, bool kExact>
+__device__ __forceinline__ bool wide_top_packed(const float (&kf)[4], int part, bool (&keep)[4],
+                                                int (&sidx)[4])
+{
+    constexpr int M = 4 * L;
+    constexpr int kIdx = M - 1;
+    constexpr int kMax = 0x7FFFFFFF, kMin = -0x7FFFFFFF - 1;
+    int own[4], p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        // +0.0f: exact keys of -0 and +0 tie
+        const int v = sortable_int(kExact ? kf[e] + 0.0f : kf[e]);
+        // (a & b) | c
+        own[e] = (int)__builtin_amdgcn_bitop3_b32((uint32_t)v, (uint32_t)~kIdx,
+                                                  (uint32_t)(4 * part + e), 0xEA);
+        p[e] = own[e];
+    }
+    const int b1 = (part & 1) == 0 ? kMax : kMin;
+    const int b2 = (part & 2) == 0 ? kMax : kMin;
+    packed_stage<1>(p, 0);
+    packed_stage<3>(p, 0);
+    packed_stage<1>(p, 0);
+    packed_stage<7>(p, b1); // 8: lane xor 1
+    packed_stage<2>(p, 0);
+    packed_stage<1>(p, 0);
+    packed_stage<15>(p, b2); // 16: lane xor 3
+    packed_stage<4>(p, b1);
+    packed_stage<2>(p, 0);
+    packed_stage<1>(p, 0);
+    if constexpr (M == 32) {
+        const int b4 = (part & 4) == 0 ? kMax : kMin;
+        packed_stage<31>(p, b4); // 32: lane xor 7
+        packed_stage<8>(p, b2);
+        packed_stage<4>(p, b1);
+        packed_stage<2>(p, 0);
+        packed_stage<1>(p, 0);
+    } else {
+        static_assert(M == 16, "group size");
+    }
+    const int lane = (int)(threadIdx.x & 63);
+    const int kth = __shfl(p[(N - 1) % 4], lane - part + (N - 1) / 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        keep[e] = own[e] >= kth;
+        sidx[e] = p[e] & kIdx;
+    }
+    // the next lane's first rank, by the DPP row shift (the group's last lane
+    // reads a value that it does not use)
+    const int next = __builtin_amdgcn_update_dpp(0, p[0], 0x101, 0xF, 0xF, true);
+    // rank 4 part + e needs no check past n, nor past the last pair
+    const auto unchecked = [&](int e) { return 4 * part + e >= (N < M ? N : M - 1); };
+    const float sum = (kf[0] + kf[1]) + (kf[2] + kf[3]);
+    bool sep = sum == sum; // no NaN (opposite infinities count as one)
+    if constexpr (kExact) {
+        const int q[5] = {p[0], p[1], p[2], p[3], next};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            sep &= unchecked(e) | ((uint32_t)(q[e] ^ q[e + 1]) > (uint32_t)kIdx);
+    } else {
+        float k[5];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) k[e] = float_of_sortable_int(p[e] & ~kIdx);
+        k[4] = float_of_sortable_int(next & ~kIdx);
+        // sorted: the largest magnitude of the four pairs is at an end
+        const float big = unchecked(3) ? fmaxf(fabsf(k[0]), fabsf(k[3]))
+                                       : fmaxf(fabsf(k[0]), fabsf(k[4]));
+        const float margin =
+            __builtin_fmaf(big, 0x1p-20f + (float)M * 0x1p-23f, kFastPairMargin);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sep &= unchecked(e) | (k[e] - k[e + 1] > margin);
+    }
     return sep;
 }
 

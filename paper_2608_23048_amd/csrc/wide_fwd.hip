@@ -9,6 +9,111 @@
 namespace roi {
 namespace {
 
+// Slots per lane that the forward without the relaxation loads ahead of
+// computing the first: more bytes in flight per wave.  It is bound by HBM and
+// issue together.  Over 1.31e9 weights on MI355X, one slot against two: 16:32
+// 2.17 and 2.01 ms, 8:16 2.08 and 1.90 ms (2.75 and 2.35 ms with keys and
+// indices sorted apart, wide.hpp; 1.73 ms at the streaming-copy rate).
+#ifndef ROI_WIDE_FWD_SLOTS
+#define ROI_WIDE_FWD_SLOTS 2
+#endif
+template <bool kRelax>
+constexpr int kWideFwdSlots = kRelax ? 1 : ROI_WIDE_FWD_SLOTS;
+
+// The hard mask of one slot, stored: W where kept, and the indices of the
+// lane's ranks 4 part .. 4 part + 3.
+template <int N>
+__device__ __forceinline__ void store_wide_mask(const FwdPiece& pc, int64_t slot, u32x2 wv,
+                                                const bool (&keep)[4])
+{
+    const uint32_t m01 = (keep[0] ? 0x0000FFFFu : 0u) | (keep[1] ? 0xFFFF0000u : 0u);
+    const uint32_t m23 = (keep[2] ? 0x0000FFFFu : 0u) | (keep[3] ? 0xFFFF0000u : 0u);
+    const u32x2 out = {wv.x & m01, wv.y & m23};
+    stream_store(out, reinterpret_cast<u32x2*>(pc.Wm + slot * 4));
+}
+
+template <int L, int N>
+__device__ __forceinline__ void store_wide_idx(const FwdPiece& pc, int64_t slot, int part,
+                                               const int (&sidx)[4])
+{
+    uint8_t* dst = pc.idx + (slot / L) * N + 4 * part;
+    if (4 * part + 4 <= N) {
+        const uint32_t w = (uint32_t)sidx[0] | ((uint32_t)sidx[1] << 8) |
+                           ((uint32_t)sidx[2] << 16) | ((uint32_t)sidx[3] << 24);
+        if constexpr (N % 4 == 0)
+            stream_store(w, reinterpret_cast<uint32_t*>(dst));
+        else
+            for (int e = 0; e < 4; ++e) dst[e] = (uint8_t)(w >> (8 * e));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * part + e < N) dst[e] = (uint8_t)sidx[e];
+    }
+}
+
+// kWideFwdSlots slots per lane, slot base + u kBlock + threadIdx.x each, all
+// loaded before the first is computed.  kFull: all of them are inside the
+// piece, so no per-lane condition makes the compiler wait for every load at a
+// join (a group's lanes are all inside or all past the end).
+template <int M, int N, bool kRelax, int kQ, bool kFull>
+__device__ __forceinline__ void fwd_wide_span(const FwdBatch& a, const FwdPiece& pc,
+                                              const NoiseKey& key, const float2* tab,
+                                              int64_t base, int64_t nslots)
+{
+    constexpr int L = M / 4;
+    constexpr int U = kWideFwdSlots<kRelax>;
+    const int part = (int)(threadIdx.x % L);
+    f32x4 pv[U];
+    u32x2 wv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t slot = base + u * kBlock + threadIdx.x;
+        if (kFull || slot < nslots) {
+            pv[u] = stream_load(reinterpret_cast<const f32x4*>(pc.phi + slot * 4));
+            wv[u] = stream_load(reinterpret_cast<const u32x2*>(pc.W + slot * 4));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t slot = base + u * kBlock + threadIdx.x;
+        if (!kFull && slot >= nslots) continue;
+        const float phi[4] = {pv[u].x, pv[u].y, pv[u].z, pv[u].w};
+        float kappa[4];
+        bool keep[4];
+        int sidx[4];
+        bool decided = false;
+        if constexpr (!kRelax) {
+            const uint4 x = philox_block(pc.block0 + (uint32_t)slot, key);
+            const float kf[4] = {fast_key_log2(phi[0], a.key_c, x.x),
+                                 fast_key_log2(phi[1], a.key_c, x.y),
+                                 fast_key_log2(phi[2], a.key_c, x.z),
+                                 fast_key_log2(phi[3], a.key_c, x.w)};
+            decided = __all(wide_top_packed<L, N, false>(kf, part, keep, sidx));
+        }
+        if (!decided) {
+            wide_keys(phi, pc.block0 + (uint32_t)slot, key, a.lambda, tab, kappa);
+            if (!kRelax || !__all(wide_top_packed<L, N, true>(kappa, part, keep, sidx)))
+                wide_top_ties<L, N>(kappa, part, keep, sidx);
+        }
+        const bool soft = kRelax && a.soft;
+        if (!soft) store_wide_mask<N>(pc, slot, wv[u], keep);
+        if (pc.idx) store_wide_idx<L, N>(pc, slot, part, sidx);
+        if constexpr (kRelax) {
+            float S[4];
+            StepRec<4> unused[N]; // not written when records are not kept
+            wide_relax_forward<L, N, false, kQ>(kappa, a.key_scale, a.inv_tau, a.exp_span,
+                                                true, S, unused);
+            if (pc.S) {
+                const f32x4 sv = {S[0], S[1], S[2], S[3]};
+                stream_store(sv, reinterpret_cast<f32x4*>(pc.S + slot * 4));
+            }
+            if (soft) // pure soft forward: W (.) S, rounded to bf16
+                stream_store(soft_product4(wv[u].x, wv[u].y, S),
+                             reinterpret_cast<u32x2*>(pc.Wm + slot * 4));
+        }
+    }
+}
+
 // Forward.  Without kRelax (the straight-through forward with neither the
 // soft mask nor the soft output) the ranks come from the hardware-log keys,
 // and a wave with any group closer than their margin recomputes the exact
@@ -17,7 +122,6 @@ namespace {
 template <int M, int N, bool kRelax, int kQ>
 __global__ __launch_bounds__(kBlock) void fwd_wide_kernel(FwdBatch a)
 {
-    constexpr int L = M / 4;
     // The exact keys read the log cells: from LDS when every group needs them
     // (kRelax), else (only groups of waves with near ties) from global memory,
     // where they stay cached, so that a block starts without a barrier.
@@ -30,66 +134,14 @@ __global__ __launch_bounds__(kBlock) void fwd_wide_kernel(FwdBatch a)
     const FwdPiece& pc = a.p[find_piece(a)];
     NoiseKey key = a.key_base;
     key.block_hi = pc.block_hi;
-    const int64_t nslots = pc.ngroups * L;
-    const int64_t stride = (int64_t)pc.nblocks * kBlock;
-    for (int64_t slot = (int64_t)(blockIdx.x - pc.first_block) * kBlock + threadIdx.x;
-         slot < nslots; slot += stride) {
-        const int part = (int)(slot % L);
-        const int64_t group = slot / L;
-        const f32x4 pv = stream_load(reinterpret_cast<const f32x4*>(pc.phi + slot * 4));
-        const u32x2 wv = stream_load(reinterpret_cast<const u32x2*>(pc.W + slot * 4));
-        const float phi[4] = {pv.x, pv.y, pv.z, pv.w};
-        float kappa[4];
-        bool keep[4];
-        int sidx[4];
-        bool decided = false;
-        if constexpr (!kRelax) {
-            const uint4 x = philox_block(pc.block0 + (uint32_t)slot, key);
-            const float kf[4] = {fast_key_log2(phi[0], a.key_c, x.x),
-                                 fast_key_log2(phi[1], a.key_c, x.y),
-                                 fast_key_log2(phi[2], a.key_c, x.z),
-                                 fast_key_log2(phi[3], a.key_c, x.w)};
-            decided = __all(wide_top<L, N, false>(kf, part, keep, sidx));
-        }
-        if (!decided) {
-            wide_keys(phi, pc.block0 + (uint32_t)slot, key, a.lambda, tab, kappa);
-            wide_top<L, N, true>(kappa, part, keep, sidx);
-        }
-        const bool soft = kRelax && a.soft;
-        if (!soft) {
-            const uint32_t m01 = (keep[0] ? 0x0000FFFFu : 0u) | (keep[1] ? 0xFFFF0000u : 0u);
-            const uint32_t m23 = (keep[2] ? 0x0000FFFFu : 0u) | (keep[3] ? 0xFFFF0000u : 0u);
-            const u32x2 out = {wv.x & m01, wv.y & m23};
-            stream_store(out, reinterpret_cast<u32x2*>(pc.Wm + slot * 4));
-        }
-        if (pc.idx) {
-            // this lane holds ranks 4 part .. 4 part + 3
-            uint8_t* dst = pc.idx + group * N + 4 * part;
-            if (4 * part + 4 <= N) {
-                const uint32_t w = (uint32_t)sidx[0] | ((uint32_t)sidx[1] << 8) |
-                                   ((uint32_t)sidx[2] << 16) | ((uint32_t)sidx[3] << 24);
-                if constexpr (N % 4 == 0)
-                    stream_store(w, reinterpret_cast<uint32_t*>(dst));
-                else
-                    for (int e = 0; e < 4; ++e) dst[e] = (uint8_t)(w >> (8 * e));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (4 * part + e < N) dst[e] = (uint8_t)sidx[e];
-            }
-        }
-        if constexpr (kRelax) {
-            float S[4];
-            StepRec<4> unused[N]; // not written when records are not kept
-            wide_relax_forward<L, N, false, kQ>(kappa, a.key_scale, a.inv_tau, a.exp_span,
-                                                true, S, unused);
-            if (pc.S) {
-                const f32x4 sv = {S[0], S[1], S[2], S[3]};
-                stream_store(sv, reinterpret_cast<f32x4*>(pc.S + slot * 4));
-            }
-            if (soft) // pure soft forward: W (.) S, rounded to bf16
-                stream_store(soft_product4(wv.x, wv.y, S), reinterpret_cast<u32x2*>(pc.Wm + slot * 4));
-        }
+    const int64_t nslots = pc.ngroups * (M / 4);
+    const int64_t span = (int64_t)kBlock * kWideFwdSlots<kRelax>;
+    for (int64_t base = (int64_t)(blockIdx.x - pc.first_block) * span; base < nslots;
+         base += (int64_t)pc.nblocks * span) {
+        if (base + span <= nslots)
+            fwd_wide_span<M, N, kRelax, kQ, true>(a, pc, key, tab, base, nslots);
+        else
+            fwd_wide_span<M, N, kRelax, kQ, false>(a, pc, key, tab, base, nslots);
     }
 }
 
@@ -189,6 +241,11 @@ FwdFn wide_fwd_for_n(int n, bool relax, int q, std::integer_sequence<int, Ns...>
 }
 
 } // namespace
+
+int64_t wide_fwd_block_slots(bool relax)
+{
+    return (int64_t)kBlock * (relax ? kWideFwdSlots<true> : kWideFwdSlots<false>);
+}
 
 FwdFn select_wide_soft_only(int m, int n, int q)
 {

@@ -305,6 +305,46 @@ def test_near_ties_bit_exact(dev, case):
         assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked differs ({want_soft})"
 
 
+WIDE_SORT = [(n, m) for m in (16, 32) for n in (1, 3, 4, m // 2 + 1, m - 1, m)]
+
+
+@pytest.mark.parametrize("n,m", WIDE_SORT)
+def test_wide_sort_edges(dev, n, m):
+    """The packed sort of the wide forwards at every kind of n (one rank, ranks
+    that end inside a lane, all): groups whose ties lie among, at and past the
+    n-th rank, infinite logits, and logits that overflow in log2 units.  Indices
+    and masked weights are the oracle's, with hardware-log and with exact keys;
+    the last group is ragged in its block."""
+    import torch
+    rows, cols, seed, step = 37, 96, 5, 2
+    groups = rows * cols // m
+    say(f"wide sort {n}:{m}")
+    rng = np.random.default_rng(100 * n + m)
+    g = oracle.keys(np.zeros(rows * cols, np.float32), 1.0, seed, step, 0).astype(np.float64)
+    target = np.sort(rng.normal(0.0, 2.0, (groups, m)), axis=1)[:, ::-1].copy()
+    for q in range(groups):  # rank r and r + 1 equal, or a few ulp apart
+        r = int(rng.integers(0, m - 1))
+        target[q, r + 1] = target[q, r] - rng.choice([0.0, 1e-7, 1e-6, 1e-5])
+    target = rng.permuted(target, axis=1)
+    L = (target.reshape(-1) - g).astype(np.float32).reshape(groups, m)
+    for q in range(0, groups, 5):
+        k = int(rng.integers(1, m + 1))
+        at = rng.permutation(m)[:k]
+        L[q, at] = rng.choice([np.inf, -np.inf, 3e38, -3e38, 1e30, -0.0], k)
+    L = L.reshape(rows, cols)
+    W = torch.randn(rows, cols, generator=torch.Generator().manual_seed(m)) + 6.0
+    W = W.to(torch.bfloat16).to(dev)
+    Lt = torch.from_numpy(L).to(dev)
+    Wm_o, _, idx_o = oracle.mask_fwd(bf16_bits(W), L, n, m, 0.5, 1.0, seed, step, 0)
+    for want_soft, want_idx in ((False, True), (True, True), (False, False)):
+        Wm, _, idx = roi.mask_fwd(W, Lt, n, m, 0.5, 1.0, seed, step, 0, want_soft=want_soft,
+                                  want_idx=want_idx)
+        torch.cuda.synchronize()
+        if want_idx:
+            assert np.array_equal(idx.cpu().numpy(), idx_o), f"indices (soft={want_soft})"
+        assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked (soft={want_soft})"
+
+
 # --------------------------------------------------------------------------- layout properties
 @pytest.mark.parametrize("tau", [1.0, 0.5, 0.4])
 def test_split_calls_equal_one_slab_call(dev, tau):
