@@ -202,9 +202,10 @@ __device__ __forceinline__ void relax_forward(float (&b)[M], float bmax0, float 
 // been dominant and falls below 2^-126 moves the total by less than 2^-35 of
 // itself, so the exp-domain and log-domain recursions agree to rounding.
 // Unlike the log-domain loop, this form keeps the first step's shift by the
-// largest key for good: each exponent b_j - bmax carries a rounding of about
-// 2^-24 |b_j - bmax| (with that of key_scale), a relative error of about
-// 4e-8 span in e_j.  span <= kExpSpanAccuracy keeps it near 1e-6.
+// largest key for good: each exponent kappa_j key_scale - bmax, one fused
+// multiply-add, carries a rounding of about 2^-24 of itself (and that of
+// key_scale), a relative error of about 4e-8 span in e_j.  span <=
+// kExpSpanAccuracy keeps it near 1e-6.
 constexpr float kExpNormalBound = 91.0f;
 constexpr float kExpSpanAccuracy = 32.0f;
 
@@ -217,14 +218,15 @@ __device__ __forceinline__ float pow_q(float om, float q)
 }
 
 template <int M, int N, bool kWantS, bool kKeep, int kQ>
-__device__ __forceinline__ void relax_forward_exp(const float (&b)[M], float bmax, float q,
-                                                  float (&S)[M], StepRec<M> (&rec)[N])
+__device__ __forceinline__ void relax_forward_exp(const float (&kappa)[M], float key_scale,
+                                                  float bmax, float q, float (&S)[M],
+                                                  StepRec<M> (&rec)[N])
 {
     static_assert(kQ >= 0 && kQ <= 2, "exp-domain recursion: kQ");
     float e[M];
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-        e[j] = __builtin_amdgcn_exp2f(b[j] - bmax);
+        e[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[j], key_scale, -bmax));
         if (kWantS) S[j] = 0.0f;
     }
 #pragma unroll
@@ -253,22 +255,24 @@ __device__ __forceinline__ void relax_forward_exp(const float (&b)[M], float bma
 // (0 above the last step), omega = 1 - mu^(k),
 //   mubar_j = sbar_j - a_j / omega_j,
 //   dL/dalpha^(k)_j = a_j + (mu_j / tau) (mubar_j - sum_l mu_l mubar_l).
-// Since omega_j mubar_j = omega_j sbar_j - a_j, with
-// X_j = omega_j sbar_j - sum_{l != j} mu_l mubar_l this is
-//   dL/dalpha^(k)_j = a_j + (mu_j / tau) (X_j - a_j),
-// one form for every j, and the sum over l != j comes from prefix and suffix
-// sums (nothing cancels when mu_j is near 1).  The rounding of X_j - a_j is
-// relative to |a_j|, which is small exactly for an entry whose mu is near 1:
-// that entry is selected at this step, so its later weights, and with them
-// a_j, are negligible.
+// Since mu_j = 1 - omega_j, this is
+//   dL/dalpha^(k)_j = a_j + (mu_j / tau) (omega_j mubar_j - sum_{l != j} mu_l mubar_l),
+// one form for every j, and the sum over l != j comes from pair or prefix and
+// suffix sums (nothing cancels when mu_j is near 1).  omega_j mubar_j carries
+// the rounding of a_j / omega_j, relative to |a_j|, which is small exactly for
+// an entry whose mu is near 1: that entry is selected at this step, so its
+// later weights, and with them a_j, are negligible.  Emulated in fp32 against
+// fp64 at the same keys, the gradient's error is within 1% of that of the form
+// with omega_j sbar_j - a_j in place of omega_j mubar_j, which costs one more
+// operation per entry and step.
 // With kFloor, an entry whose 1 - mu fell below FLT_MIN at an updating step
-// had its log floored, so no derivative flows through it: mubar_j = sbar_j and
-// dL/dalpha^(k)_j = a_j + (mu_j / tau) X_j.  The records of relax_forward hold
-// max(1 - mu, FLT_MIN) there, so such an entry reads exactly FLT_MIN: it takes
-// a_j = 0 in both places, which also keeps a_j / omega_j finite.  X_j then uses
-// FLT_MIN for an omega_j below it, a change below FLT_MIN |sbar_j|.  Without
-// kFloor the caller has ruled the floor out (the exp-domain form's span
-// bound, whose records hold 1 - mu itself).
+// had its log floored, so no derivative flows through it: mubar_j = sbar_j.
+// The records of relax_forward hold max(1 - mu, FLT_MIN) there, so such an
+// entry reads exactly FLT_MIN: it takes a_j = 0 in mubar_j, which also keeps
+// a_j / omega_j finite, and omega_j mubar_j uses FLT_MIN for an omega_j below
+// it, a change below FLT_MIN |sbar_j|.  Without kFloor the caller has ruled
+// the floor out (the exp-domain form's span bound, whose records hold 1 - mu
+// itself).
 template <int M, int N, bool kTauIsOne, bool kFloor>
 __device__ __forceinline__ void relax_backward(const StepRec<M> (&rec)[N], const float (&sbar)[M],
                                                float inv_tau, float (&abar)[M])
@@ -276,25 +280,24 @@ __device__ __forceinline__ void relax_backward(const StepRec<M> (&rec)[N], const
 #pragma unroll
     for (int k = N - 1; k >= 0; --k) {
         const bool has_next = (k + 1 < N);
-        float t[M], a_in[M];
+        float t[M], mubar[M];
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            float mubar = sbar[j];
-            a_in[j] = 0.0f;
+            mubar[j] = sbar[j];
             if (has_next) {
                 const float om = rec[k].om[j];
-                a_in[j] = !kFloor || om > kFltMin ? abar[j] : 0.0f;
-                mubar = __builtin_fmaf(-a_in[j], __builtin_amdgcn_rcpf(om), sbar[j]);
+                const float a = !kFloor || om > kFltMin ? abar[j] : 0.0f;
+                mubar[j] = __builtin_fmaf(-a, __builtin_amdgcn_rcpf(om), sbar[j]);
             }
-            t[j] = rec[k].mu[j] * mubar;
+            t[j] = rec[k].mu[j] * mubar[j];
         }
         float q[M], unused;
         sums_but_one<M>(t, q, unused);
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            const float x = __builtin_fmaf(rec[k].om[j], sbar[j], -q[j]);
+            const float x = __builtin_fmaf(rec[k].om[j], mubar[j], -q[j]);
             const float m_t = kTauIsOne ? rec[k].mu[j] : rec[k].mu[j] * inv_tau;
-            abar[j] = has_next ? __builtin_fmaf(m_t, x - a_in[j], abar[j]) : m_t * x;
+            abar[j] = has_next ? __builtin_fmaf(m_t, x, abar[j]) : m_t * x;
         }
     }
 }

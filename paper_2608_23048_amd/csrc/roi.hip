@@ -411,7 +411,8 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
                 StepRec<M> unused[N]; // not written when records are not kept
                 const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
                 if (span <= a.exp_span)
-                    relax_forward_exp<M, N, true, false, kQ>(b, bmax, a.inv_tau, S, unused);
+                    relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
+                                                     unused);
                 else
                     relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
                 if (pc.S) {
@@ -493,7 +494,8 @@ __device__ __forceinline__ void soft_lane_chunk(const FwdBatch& a, const FwdPiec
             scaled_keys<M, false>(kappa, a.key_scale, b, bmax);
             relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
         } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
-            relax_forward_exp<M, N, true, false, kQ>(b, bmax, a.inv_tau, S, unused);
+            relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
+                                                     unused);
         } else {
             relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
         }
@@ -555,7 +557,8 @@ __device__ __forceinline__ void bwd_group4(const BwdBatch& a, const BwdPiece& pc
         relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
         relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
     } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
-        relax_forward_exp<M, N, false, true, kQ>(b, bmax, a.inv_tau, S_unused, rec);
+        relax_forward_exp<M, N, false, true, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S_unused,
+                                                  rec);
         relax_backward<M, N, kQ == 1, false>(rec, sbar, a.inv_tau, abar);
     } else {
         relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);

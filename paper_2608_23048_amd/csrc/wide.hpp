@@ -39,12 +39,16 @@ __device__ __forceinline__ float lane_xor(float v)
     return __int_as_float(x);
 }
 
+// Value of the group's other quad of lanes, for a v that is the same in every
+// lane of a quad (lane xor 7 is then as good as xor 4, and one DPP less).
+__device__ __forceinline__ float other_quad(float v) { return lane_xor<7>(v); }
+
 template <int L>
 __device__ __forceinline__ float group_max(float v)
 {
     v = fmaxf(v, lane_xor<1>(v));
     if constexpr (L >= 4) v = fmaxf(v, lane_xor<2>(v));
-    if constexpr (L >= 8) v = fmaxf(v, lane_xor<4>(v));
+    if constexpr (L >= 8) v = fmaxf(v, other_quad(v));
     return v;
 }
 
@@ -58,8 +62,8 @@ __device__ __forceinline__ float sum_other_lanes(float t)
     const float s1 = t + o1; // pair sum
     float other = o1 + lane_xor<2>(s1);
     if constexpr (L == 8) {
-        const float s2 = s1 + lane_xor<2>(s1); // quad sum
-        other += lane_xor<4>(s2);
+        const float s2 = s1 + lane_xor<2>(s1); // quad sum, the same bits in the quad's lanes
+        other += other_quad(s2);
     }
     return other;
 }
@@ -74,7 +78,7 @@ __device__ __forceinline__ float group_min(float v)
 {
     v = fminf(v, lane_xor<1>(v));
     if constexpr (L >= 4) v = fminf(v, lane_xor<2>(v));
-    if constexpr (L >= 8) v = fminf(v, lane_xor<4>(v));
+    if constexpr (L >= 8) v = fminf(v, other_quad(v));
     return v;
 }
 
@@ -335,7 +339,8 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
     if (kQ >= 0 && span <= exp_span) { // the same on all lanes of the group
         float ex[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ex[e] = __builtin_amdgcn_exp2f(b[e] - bmax0);
+        for (int e = 0; e < 4; ++e)
+            ex[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[e], c, -bmax0));
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             float others[4], t;
@@ -395,11 +400,10 @@ __device__ __forceinline__ void wide_relax_backward(const StepRec<4> (&rec)[N],
 #pragma unroll
     for (int k = N - 1; k >= 0; --k) {
         const bool has_next = (k + 1 < N);
-        float t[4], a_in[4];
+        float t[4], mubar[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float mubar = sbar[e];
-            a_in[e] = 0.0f;
+            mubar[e] = sbar[e];
             if (has_next) {
                 const float om = rec[k].om[e];
                 const bool live = !kFloor || om >= kFltMin;
@@ -409,10 +413,9 @@ __device__ __forceinline__ void wide_relax_backward(const StepRec<4> (&rec)[N],
                 // the compiler does not compute them ahead of the choice and
                 // hold them in registers beside the records.
                 const float rinv = __builtin_amdgcn_rcpf(live ? om : __builtin_inff());
-                mubar = __builtin_fmaf(-abar[e], rinv, sbar[e]);
-                a_in[e] = live ? abar[e] : 0.0f;
+                mubar[e] = __builtin_fmaf(-abar[e], rinv, sbar[e]);
             }
-            t[e] = rec[k].mu[e] * mubar;
+            t[e] = rec[k].mu[e] * mubar[e];
         }
         // Sum over the group's entries but e: the other lanes' sum enters the
         // two pair sums of this lane, so each is one add from them (no
@@ -423,9 +426,9 @@ __device__ __forceinline__ void wide_relax_backward(const StepRec<4> (&rec)[N],
         const float q[4] = {t[1] + pbe, t[0] + pbe, pae + t[3], pae + t[2]};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float x = __builtin_fmaf(rec[k].om[e], sbar[e], -q[e]);
+            const float x = __builtin_fmaf(rec[k].om[e], mubar[e], -q[e]);
             const float m_t = kTauIsOne ? rec[k].mu[e] : rec[k].mu[e] * inv_tau;
-            abar[e] = has_next ? __builtin_fmaf(m_t, x - a_in[e], abar[e]) : m_t * x;
+            abar[e] = has_next ? __builtin_fmaf(m_t, x, abar[e]) : m_t * x;
         }
     }
 }
