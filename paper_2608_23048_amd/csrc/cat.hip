@@ -3,8 +3,10 @@
 // Efficiency"): one logit alpha_c per feasible n-hot mask c of a group,
 // Pr(c) = softmax(alpha)_c, sampled with Gumbel-Softmax.
 //
-// One lane per group of m in {4, 8} weights; the C = binom(m, n) candidate
-// masks are compile-time bitmasks in lexicographic order of their index sets.
+// One lane per group of m in {4, 8} weights (up to 8 candidates), or the
+// candidates of a group over up to three waves (28 to 70); the C = binom(m, n)
+// candidate masks are compile-time bitmasks in lexicographic order of their
+// index sets.
 // Keys kappa_c = alpha_c / lambda + g_c with the noise of element 4 B Q + c
 // (B = ceil(C / 4) Philox blocks per group Q).  The hard sample is the
 // candidate of largest key (ties to the lower candidate), the relaxed mask
@@ -15,7 +17,9 @@
 // keys); S and the backward use the exact keys.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <utility>
 
 #include "common.hpp"
@@ -115,9 +119,8 @@ __device__ __forceinline__ void store_cat(float* p, const float (&a)[C])
     }
 }
 
-// Threads per block: the tile of a block's logits (block * C floats) is staged
-// through LDS and must fit in 64 KB.
-constexpr int cat_block(int C) { return C > 64 ? 128 : 256; }
+// Threads (and groups) per block of the kernels with one lane per group.
+constexpr int kCatBlock = 256;
 // Groups with at least 8 logits (32 bytes) are staged: read per lane from
 // global memory, their 32-280-byte strides would touch up to 8x more cache
 // lines per load instruction than a contiguous 16-byte-per-lane stream.
@@ -215,10 +218,10 @@ __device__ __forceinline__ void cat_softmax(float (&k)[C], float scale)
 }
 
 template <int M, int N, bool kSoft>
-__global__ __launch_bounds__(cat_block(Candidates<M, N>::C)) void cat_fwd_kernel(CatArgs a)
+__global__ __launch_bounds__(kCatBlock) void cat_fwd_kernel(CatArgs a)
 {
     constexpr int C = Candidates<M, N>::C;
-    constexpr int B = cat_block(C);
+    constexpr int B = kCatBlock;
     constexpr bool kStage = cat_staged(C);
     // The log cells in LDS only when every group takes the exact keys (kSoft);
     // otherwise they serve groups whose top two keys are close and are read
@@ -335,22 +338,18 @@ __device__ __forceinline__ void cat_keys_from_noise(const float (&alpha)[C], con
 // One chunk of B groups of the categorical backward.  The loads go out first:
 // the group's W and dL/dW_masked, its logits (per lane, or for the staged
 // tile this thread's share of the block's contiguous logits), and the log
-// cells.  With up to 8 candidates the noise -- C Philox words and 2C
-// logarithms per group, most of the arithmetic -- needs none of them and runs
-// while they are in flight; with more, the C noise values and the tile share
-// would not fit in registers beside each other, and each key is formed as its
-// noise is drawn, after the loads.  kFull: all B groups are inside the
-// array, so no per-lane condition makes the compiler wait for every load at
-// a join.
+// cells.  The noise -- C Philox words and 2C logarithms per group, most of the
+// arithmetic -- needs none of them and runs while they are in flight.  kFull:
+// all B groups are inside the array, so no per-lane condition makes the
+// compiler wait for every load at a join.
 template <int M, int N, bool kFull>
 __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, float2* tab,
                                               int64_t base)
 {
     constexpr int C = Candidates<M, N>::C;
-    constexpr int B = cat_block(C);
+    constexpr int B = kCatBlock;
     constexpr bool kStage = cat_staged_bwd(C);
-    constexpr bool kNoiseFirst = C <= 8;
-    constexpr int kShare = kStage && kNoiseFirst ? C / 2 : 1; // 8-byte tile pieces per thread
+    constexpr int kShare = kStage ? C / 2 : 1; // 8-byte tile pieces per thread
     const int here = kFull ? B : (int)(a.ngroups - base);
     const int64_t q = base + threadIdx.x;
     const bool live = kFull || (int)threadIdx.x < here;
@@ -362,7 +361,7 @@ __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, flo
         load_bf16_pairs<M>(a.G + q * M, g);
     }
     if constexpr (kStage) {
-        if constexpr (kFull && kNoiseFirst) {
+        if constexpr (kFull) {
             const f32x2v* src = reinterpret_cast<const f32x2v*>(a.alpha + base * C);
 #pragma unroll
             for (int i = 0; i < kShare; ++i) share[i] = stream_load(src + threadIdx.x + i * B);
@@ -372,17 +371,15 @@ __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, flo
     }
     const float4 cells = log_cells_of_lane();
     __builtin_amdgcn_sched_barrier(0);
-    float ng[kNoiseFirst ? C : 1];
+    float ng[C];
     uint32_t x[C];
     cat_words<C>(a.group0 + (uint64_t)q, a.key, x);
     publish_log_table(tab, cells);
-    if constexpr (kNoiseFirst) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) ng[c] = neg_gumbel_from_word(x[c], tab);
-    }
+    for (int c = 0; c < C; ++c) ng[c] = neg_gumbel_from_word(x[c], tab);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (kStage) {
-        if constexpr (kFull && kNoiseFirst) {
+        if constexpr (kFull) {
             f32x2v* dst = reinterpret_cast<f32x2v*>(tile);
 #pragma unroll
             for (int i = 0; i < kShare; ++i) dst[threadIdx.x + i * B] = share[i];
@@ -400,10 +397,7 @@ __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, flo
     if (live) {
         // the keys the forward sampled, and their softmax
         float y[C];
-        if constexpr (kNoiseFirst)
-            cat_keys_from_noise<C>(alpha, ng, a.lambda, y);
-        else
-            cat_exact_keys<C>(alpha, x, a.lambda, tab, y);
+        cat_keys_from_noise<C>(alpha, ng, a.lambda, y);
         cat_softmax<C>(y, kLog2e * a.inv_tau);
         // Straight-through: dL/dS = dL/dW_masked (.) W; ybar_c = sum_{j in c} sbar_j.
         float sbar[M];
@@ -440,10 +434,10 @@ __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, flo
 }
 
 template <int M, int N>
-__global__ __launch_bounds__(cat_block(Candidates<M, N>::C)) void cat_bwd_kernel(CatArgs a)
+__global__ __launch_bounds__(kCatBlock) void cat_bwd_kernel(CatArgs a)
 {
     constexpr int C = Candidates<M, N>::C;
-    constexpr int B = cat_block(C);
+    constexpr int B = kCatBlock;
     __shared__ float tile[cat_staged_bwd(C) ? B * C : 2];
     // Every group takes the exact keys; the block's waves share one copy of
     // the log cells in LDS (noise.hpp).
@@ -459,15 +453,557 @@ __global__ __launch_bounds__(cat_block(Candidates<M, N>::C)) void cat_bwd_kernel
     }
 }
 
+// ---- groups with many candidates (C = 28, 56, 70: m = 8, n = 2 .. 6)
+//
+// One lane per group would hold C noise values, keys and gradients in
+// registers and one wave 64 C logits in LDS: two waves per SIMD at 4:8, each
+// waiting in turn for its logits, its arithmetic and its stores.  Here the
+// candidates of a group are split over kParts waves of a block: lane l of
+// wave (row, part) takes the 4 kBlocks candidates of Philox blocks
+// part kBlocks .. of group 64 row + l, so that every lane has the same work
+// (70 candidates are 18 Philox blocks: three parts of six).  The block's
+// logits are one contiguous span, staged through LDS, and the noise -- most of
+// the arithmetic, and independent of every input -- is computed while they are
+// in flight.
+// Group maxima, sums and dot products go through small LDS arrays.
+// 1.5B-class layer at 4:8 (5.85e6 groups) on MI355X: forward 924 us with one
+// lane per group, 363 us so (284 us at the streaming-copy rate); backward
+// 1433 us and 601 us (537 us).
+// Waves per SIMD the split kernels are compiled for (at most 128 VGPRs; five
+// spill in most of them).
+constexpr int kSplitWaves = 4;
+// Up to 8 candidates fit one lane's registers beside their noise, and take
+// the kernels above; 28 is the next count.
+constexpr bool cat_split(int C) { return C >= 28; }
+constexpr int cat_parts(int C) { return C > 64 ? 3 : (C > 32 ? 2 : 1); }
+// Rows of 64 groups per block.
+constexpr int cat_rows(int C) { return C > 64 ? 1 : 2; }
+
+template <int M, int N>
+struct CatSplit {
+    static constexpr int C = Candidates<M, N>::C;
+    static constexpr int kParts = cat_parts(C);
+    static constexpr int kRows = cat_rows(C);
+    static constexpr int kPhilox = (C + 3) / 4;      // Philox blocks per group
+    static constexpr int kBlocks = kPhilox / kParts; // per part
+    static constexpr int K = 4 * kBlocks;            // candidates per lane
+    static constexpr int kPad = kParts * K - C;      // past the end, in the last part
+    static constexpr int kGroups = 64 * kRows;       // groups per block
+    static constexpr int kThreads = kGroups * kParts;
+    static constexpr int kFloats = kGroups * C;      // logits per block
+    // 16-byte vectors per thread, and the tile they fill.
+    static constexpr int kShare = (kFloats / 4 + kThreads - 1) / kThreads;
+    static constexpr int kTile = kShare * kThreads * 4;
+    static_assert(kPhilox % kParts == 0 && C % 2 == 0 && kPad % 2 == 0 && kPad < K, "split");
+};
+
+// The logits of a full block (kFloats floats, 16-byte aligned): each thread
+// loads its share, 16 bytes at a time, ahead of the noise, and stores it to
+// the tile after.  The last loads may lie half beyond the span: they read the
+// last vector again, into the tile's padding, so that no load stands under a
+// condition (after which the compiler would wait for all of them).  Loads
+// that write LDS themselves would need no registers, but the compiler waits
+// for them before the next access to LDS, and the noise reads its table there.
+template <typename Sp>
+__device__ __forceinline__ void load_share(const float* g, f32x4 (&share)[Sp::kShare])
+{
+    constexpr int kVecs = Sp::kFloats / 4;
+#pragma unroll
+    for (int i = 0; i < Sp::kShare; ++i) {
+        const int v = i * Sp::kThreads + (int)threadIdx.x;
+        share[i] = stream_load(reinterpret_cast<const f32x4*>(g) + (v < kVecs ? v : kVecs - 1));
+    }
+}
+
+template <typename Sp>
+__device__ __forceinline__ void store_share(const f32x4 (&share)[Sp::kShare], float* tile)
+{
+#pragma unroll
+    for (int i = 0; i < Sp::kShare; ++i)
+        reinterpret_cast<f32x4*>(tile)[i * Sp::kThreads + (int)threadIdx.x] = share[i];
+}
+
+// The lane's place: its group's row in the block, and its first candidate.
+template <typename Sp>
+struct CatLane {
+    int part, row, c0;
+    __device__ __forceinline__ CatLane()
+    {
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        part = wave / Sp::kRows;
+        row = (wave % Sp::kRows) * 64 + (int)(threadIdx.x & 63);
+        c0 = part * Sp::K;
+    }
+    // candidate i of the lane exists (known at compile time for most i)
+    __device__ __forceinline__ bool has(int i) const
+    {
+        return i < Sp::K - Sp::kPad || part + 1 < Sp::kParts;
+    }
+};
+
+// The noise of the lane's candidates: f(word) for each.  One Philox block at
+// a time, finished where it is written (pin, and the barrier that keeps the
+// compiler from interleaving the blocks), so that the kernel's registers are
+// those of the keys, not of the noise in the making.
+template <typename Sp, typename F>
+__device__ __forceinline__ void split_noise(uint64_t Q, int part, const NoiseKey& key,
+                                            float (&v)[Sp::K], F f)
+{
+    const uint64_t first = Q * Sp::kPhilox + (uint32_t)(part * Sp::kBlocks);
+#pragma unroll
+    for (int b = 0; b < Sp::kBlocks; ++b) {
+        const uint4 x = philox_block64(first + b, key);
+        v[4 * b] = f(x.x);
+        v[4 * b + 1] = f(x.y);
+        v[4 * b + 2] = f(x.z);
+        v[4 * b + 3] = f(x.w);
+#pragma unroll
+        for (int i = 4 * b; i < 4 * b + 4; ++i) pin(v[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The lane's logits from the tile (8-byte reads: rows of an odd number of
+// 8-byte words at C = 70, so a wave's reads spread over the banks).
+template <typename Sp>
+__device__ __forceinline__ void split_logits(const float* tile, const CatLane<Sp>& ln,
+                                             float (&alpha)[Sp::K])
+{
+    const f32x2v* p = reinterpret_cast<const f32x2v*>(tile + ln.row * Sp::C + ln.c0);
+#pragma unroll
+    for (int i = 0; i < Sp::K; i += 2) {
+        const f32x2v v = ln.has(i) ? p[i / 2] : f32x2v{0.0f, 0.0f};
+        alpha[i] = v.x;
+        alpha[i + 1] = v.y;
+    }
+}
+
+// Exact keys in place, kappa = fl(fl(alpha / lambda) + g), from the noise k =
+// -g (lambda = 1 is a wave-uniform branch without the division); entries past
+// the end are -inf (below every key, weight 0).
+template <typename Sp>
+__device__ __forceinline__ void split_keys(const CatLane<Sp>& ln, const float (&alpha)[Sp::K],
+                                           float lambda, float (&k)[Sp::K])
+{
+    if (__builtin_amdgcn_readfirstlane(__float_as_uint(lambda)) == 0x3F800000u) {
+#pragma unroll
+        for (int i = 0; i < Sp::K; ++i) k[i] = alpha[i] - k[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < Sp::K; ++i) {
+            k[i] = alpha[i] / lambda - k[i];
+            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0); // few quotients in the making
+        }
+    }
+#pragma unroll
+    for (int i = Sp::K - Sp::kPad; i < Sp::K; ++i) k[i] = ln.has(i) ? k[i] : -INFINITY;
+}
+
+// Whether candidate c (none past the last) holds element j.
+template <int M, int N>
+constexpr bool in_candidate(int c, int j)
+{
+    return c < Candidates<M, N>::C && ((kCand<M, N>.mask[c] >> j) & 1) != 0;
+}
+
+// Calls f with each part's candidate numbers as compile-time constants:
+// f(integral_constant<int, c0>) runs for the wave's own part.
+template <typename Sp, int P = 0, typename F>
+__device__ __forceinline__ void for_part(int part, F&& f)
+{
+    if constexpr (P + 1 < Sp::kParts) {
+        if (part == P)
+            f(std::integral_constant<int, P * Sp::K>{});
+        else
+            for_part<Sp, P + 1>(part, f);
+    } else {
+        f(std::integral_constant<int, P * Sp::K>{});
+    }
+}
+
+// Reads the kParts values that the parts of a group stored at x[part][row].
+template <typename Sp, typename Op>
+__device__ __forceinline__ float over_parts(const float (*x)[Sp::kGroups], int row, Op op)
+{
+    float v = x[0][row];
+#pragma unroll
+    for (int p = 1; p < Sp::kParts; ++p) v = op(v, x[p][row]);
+    return v;
+}
+
+// The expanded masks of the candidates: entry c clears the elements outside
+// c's subset from a group's eight bf16 values.
+struct alignas(16) Keep8 {
+    uint32_t w[4];
+};
+template <int N>
+struct Keep8Table {
+    Keep8 e[Candidates<8, N>::C];
+};
+template <int N>
+constexpr Keep8Table<N> make_keep8()
+{
+    Keep8Table<N> t{};
+    for (int c = 0; c < Candidates<8, N>::C; ++c)
+        for (int j = 0; j < 8; ++j)
+            if ((kCand<8, N>.mask[c] >> j) & 1)
+                t.e[c].w[j / 2] |= j % 2 ? 0xFFFF0000u : 0x0000FFFFu;
+    return t;
+}
+template <int N>
+__device__ const Keep8Table<N> kKeep8 = make_keep8<N>();
+
+// The candidate of largest key among the parts' (key, candidate) pairs, ties
+// to the lower candidate (parts hold ascending candidates).
+template <typename Sp>
+__device__ __forceinline__ int best_of_parts(const float (*top)[Sp::kGroups],
+                                             const int (*best)[Sp::kGroups], int row)
+{
+    float t = top[0][row];
+    int b = best[0][row];
+#pragma unroll
+    for (int p = 1; p < Sp::kParts; ++p) {
+        const bool better = top[p][row] > t;
+        b = better ? best[p][row] : b;
+        t = better ? top[p][row] : t;
+    }
+    return b;
+}
+
+// The lane's largest key, ties to the lower candidate.
+template <typename Sp>
+__device__ __forceinline__ void lane_argmax(const CatLane<Sp>& ln, const float (&k)[Sp::K],
+                                            float& top, int& best)
+{
+    top = k[0];
+    best = 0;
+#pragma unroll
+    for (int i = 1; i < Sp::K; ++i) {
+        const bool better = k[i] > top;
+        best = better ? i : best;
+        top = better ? k[i] : top;
+    }
+    best += ln.c0;
+}
+
+template <int M, int N, bool kSoft>
+struct CatFwdShared {
+    using Sp = CatSplit<M, N>;
+    alignas(16) float tile[Sp::kTile];
+    float4 tab[kLogCells / 2];
+    float x_top[Sp::kParts][Sp::kGroups];
+    float x_second[kSoft ? 1 : Sp::kParts][Sp::kGroups];
+    int x_best[Sp::kParts][Sp::kGroups];
+    float x_sum[kSoft ? Sp::kParts : 1][kSoft ? M + 1 : 1][Sp::kGroups];
+};
+
+// The forward of kGroups groups from `base` (kFull: all are inside the array).
+template <int M, int N, bool kSoft, bool kFull>
+__device__ __forceinline__ void cat_fwd_split_tile(const CatArgs& a, CatFwdShared<M, N, kSoft>& sh,
+                                                   int64_t base)
+{
+    using Sp = CatSplit<M, N>;
+    constexpr int K = Sp::K;
+    const CatLane<Sp> ln;
+    const int here = kFull ? Sp::kGroups : (int)(a.ngroups - base);
+    const bool live = kFull || ln.row < here;
+    const int64_t q = base + ln.row;
+    const bool writes = ln.part == 0 && live; // one part stores the group's outputs
+    const float4 cells = log_cells_of_lane();
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t w[M / 2];
+    f32x4 share[Sp::kShare];
+    if constexpr (kFull) load_share<Sp>(a.alpha + base * Sp::C, share);
+    if (live) load_bf16_pairs<M>(a.W + q * M, w); // by every part: no condition
+    float2* tab = reinterpret_cast<float2*>(sh.tab);
+    publish_log_table(tab, cells);
+    const uint64_t Q = a.group0 + (uint64_t)q;
+    const auto exact_noise = [&](uint32_t x) { return neg_gumbel_from_word(x, tab); };
+    float k[K]; // the noise, then the keys
+    if constexpr (kSoft)
+        split_noise<Sp>(Q, ln.part, a.key, k, exact_noise);
+    else
+        split_noise<Sp>(Q, ln.part, a.key, k, [](uint32_t x) { return fast_noise_log2(x); });
+    if constexpr (kFull)
+        store_share<Sp>(share, sh.tile);
+    else
+        tile_in<Sp::kThreads>(a.alpha + base * Sp::C, sh.tile, here * Sp::C);
+    __syncthreads();
+    float alpha[K];
+    split_logits<Sp>(sh.tile, ln, alpha);
+    bool exact = true;
+    int best = 0;
+    if constexpr (!kSoft) {
+        // Hardware-log keys: decided when the top two of the group are
+        // further apart than the error of two keys (noise.hpp); a lower
+        // key's larger |K| widens the margin by less than its distance.
+        // The sum tells a NaN, and an infinite key makes the margin so.
+        float sum = 0.0f, top = -INFINITY, second = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (!ln.has(i)) continue;
+            const float v = __builtin_fmaf(alpha[i], a.key_c, k[i]);
+            sum += v;
+            second = __builtin_amdgcn_fmed3f(top, second, v);
+            const bool better = v > top;
+            best = better ? i : best;
+            top = better ? v : top;
+        }
+        sh.x_top[ln.part][ln.row] = sum == sum ? top : NAN;
+        sh.x_second[ln.part][ln.row] = second;
+        sh.x_best[ln.part][ln.row] = ln.c0 + best;
+        __syncthreads();
+        // the same in every part of the group
+        best = best_of_parts<Sp>(sh.x_top, sh.x_best, ln.row);
+        top = -INFINITY;
+        second = -INFINITY;
+        float nan = 0.0f;
+#pragma unroll
+        for (int p = 0; p < Sp::kParts; ++p) {
+            const float t = sh.x_top[p][ln.row], s = sh.x_second[p][ln.row];
+            nan += t;
+            second = fmaxf(fmaxf(second, s), fminf(top, t));
+            top = fmaxf(top, t);
+        }
+        const float margin = __builtin_fmaf(fmaxf(fabsf(top), fabsf(second)), 0x1p-20f,
+                                            kFastPairMargin);
+        exact = nan != nan || !(top - second > margin);
+        exact = __syncthreads_or(live && exact) != 0;
+    }
+    if (exact) { // uniform over the block
+        if constexpr (!kSoft) { // rare: words and logits anew, not held in registers
+            uint64_t again = Q;
+            asm volatile("" : "+v"(again));
+            split_noise<Sp>(again, ln.part, a.key, k, exact_noise);
+            split_logits<Sp>(sh.tile, ln, alpha);
+        }
+        split_keys<Sp>(ln, alpha, a.lambda, k);
+        float top;
+        lane_argmax<Sp>(ln, k, top, best);
+        sh.x_top[ln.part][ln.row] = top;
+        sh.x_best[ln.part][ln.row] = best;
+        __syncthreads();
+        best = best_of_parts<Sp>(sh.x_top, sh.x_best, ln.row);
+    }
+    if (writes) {
+        const Keep8 keep = kKeep8<N>.e[best];
+        const u32x4 v = {w[0] & keep.w[0], w[1] & keep.w[1], w[2] & keep.w[2],
+                         w[3] & keep.w[3]};
+        stream_store(v, reinterpret_cast<u32x4*>(a.Wm + q * M));
+        if (a.choice) stream_store((uint8_t)best, a.choice + q);
+    }
+    if constexpr (kSoft) {
+        const auto larger = [](float u, float v) { return fmaxf(u, v); };
+        const float mx = over_parts<Sp>(sh.x_top, ln.row, larger);
+        const float scale = kLog2e * a.inv_tau;
+        float t = 0.0f, S[M];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            k[i] = __builtin_amdgcn_exp2f((k[i] - mx) * scale);
+            t += k[i];
+        }
+        for_part<Sp>(ln.part, [&](auto c0) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) S[j] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+#pragma unroll
+                for (int j = 0; j < M; ++j)
+                    if (in_candidate<M, N>(c0 + i, j))
+                        S[j] += k[i];
+            }
+        });
+#pragma unroll
+        for (int j = 0; j < M; ++j) sh.x_sum[ln.part][j][ln.row] = S[j];
+        sh.x_sum[ln.part][M][ln.row] = t;
+        __syncthreads();
+        if (writes && a.S) {
+            float total = 0.0f;
+#pragma unroll
+            for (int j = 0; j < M; ++j) S[j] = 0.0f;
+#pragma unroll
+            for (int p = 0; p < Sp::kParts; ++p) {
+                total += sh.x_sum[p][M][ln.row];
+#pragma unroll
+                for (int j = 0; j < M; ++j) S[j] += sh.x_sum[p][j][ln.row];
+            }
+            const float r = __builtin_amdgcn_rcpf(total);
+#pragma unroll
+            for (int j = 0; j < M; ++j) S[j] *= r;
+            store_f32<M>(a.S + q * M, S);
+        }
+    }
+    __syncthreads(); // the tile and the exchange arrays are used again
+}
+
+template <int M, int N, bool kSoft>
+__global__ __launch_bounds__((CatSplit<M, N>::kThreads), kSplitWaves) void cat_fwd_split_kernel(
+    CatArgs a)
+{
+    constexpr int G = CatSplit<M, N>::kGroups;
+    __shared__ CatFwdShared<M, N, kSoft> sh;
+    for (int64_t base = (int64_t)blockIdx.x * G; base < a.ngroups; base += (int64_t)gridDim.x * G) {
+        if (base + G <= a.ngroups) // uniform over the block
+            cat_fwd_split_tile<M, N, kSoft, true>(a, sh, base);
+        else
+            cat_fwd_split_tile<M, N, kSoft, false>(a, sh, base);
+    }
+}
+
+template <int M, int N>
+struct CatBwdShared {
+    using Sp = CatSplit<M, N>;
+    alignas(16) float tile[Sp::kTile];
+    float4 tab[kLogCells / 2];
+    float x_top[Sp::kParts][Sp::kGroups];
+    float x_sum[Sp::kParts][Sp::kGroups];
+    float x_dot[Sp::kParts][Sp::kGroups];
+};
+
+// The backward of kGroups groups from `base` (kFull: all are inside the array).
+template <int M, int N, bool kFull>
+__device__ __forceinline__ void cat_bwd_split_tile(const CatArgs& a, CatBwdShared<M, N>& sh,
+                                                   int64_t base)
+{
+    using Sp = CatSplit<M, N>;
+    constexpr int K = Sp::K;
+    const CatLane<Sp> ln;
+    const int here = kFull ? Sp::kGroups : (int)(a.ngroups - base);
+    const bool live = kFull || ln.row < here;
+    const int64_t q = base + ln.row;
+    const float4 cells = log_cells_of_lane();
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t w[M / 2] = {}, g[M / 2] = {};
+    f32x4 share[Sp::kShare];
+    if constexpr (kFull) load_share<Sp>(a.alpha + base * Sp::C, share);
+    if (live) { // every part of a group reads them; all but one hit the cache
+        load_bf16_pairs<M>(a.W + q * M, w);
+        load_bf16_pairs<M>(a.G + q * M, g);
+    }
+    float k[K]; // -g, then the keys, then the weights
+    {
+        float2* tab = reinterpret_cast<float2*>(sh.tab);
+        publish_log_table(tab, cells);
+        split_noise<Sp>(a.group0 + (uint64_t)q, ln.part, a.key, k,
+                        [&](uint32_t x) { return neg_gumbel_from_word(x, tab); });
+    }
+    if constexpr (kFull)
+        store_share<Sp>(share, sh.tile);
+    else
+        tile_in<Sp::kThreads>(a.alpha + base * Sp::C, sh.tile, here * Sp::C);
+    __syncthreads();
+    {
+        float alpha[K];
+        split_logits<Sp>(sh.tile, ln, alpha);
+        split_keys<Sp>(ln, alpha, a.lambda, k);
+    }
+    float mx = k[0];
+#pragma unroll
+    for (int i = 1; i < K; ++i) mx = fmaxf(mx, k[i]);
+    sh.x_top[ln.part][ln.row] = mx;
+    if constexpr (Sp::kParts > 1) __syncthreads();
+    mx = over_parts<Sp>(sh.x_top, ln.row, [](float u, float v) { return fmaxf(u, v); });
+    // Straight-through: dL/dS = dL/dW_masked (.) W; ybar_c = sum_{j in c} sbar_j.
+    float sbar[M];
+#pragma unroll
+    for (int i = 0; i < M / 2; ++i) {
+        sbar[2 * i] = bf16_bits_to_float(g[i] & 0xFFFFu) * bf16_bits_to_float(w[i] & 0xFFFFu);
+        sbar[2 * i + 1] = bf16_bits_to_float(g[i] >> 16) * bf16_bits_to_float(w[i] >> 16);
+    }
+    const float scale = kLog2e * a.inv_tau;
+    float t = 0.0f, dot = 0.0f, ybar[K];
+    for_part<Sp>(ln.part, [&](auto c0) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int j = 0; j < M; ++j)
+                if (in_candidate<M, N>(c0 + i, j))
+                    acc += sbar[j];
+            ybar[i] = acc;
+        }
+    });
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        k[i] = __builtin_amdgcn_exp2f((k[i] - mx) * scale);
+        t += k[i];
+        dot = __builtin_fmaf(k[i], ybar[i], dot);
+    }
+    sh.x_sum[ln.part][ln.row] = t;
+    sh.x_dot[ln.part][ln.row] = dot;
+    if constexpr (Sp::kParts > 1) __syncthreads();
+    const auto add = [](float u, float v) { return u + v; };
+    const float r = __builtin_amdgcn_rcpf(over_parts<Sp>(sh.x_sum, ln.row, add));
+    // ybar - <y, ybar> in two steps, first from the rounded <y, ybar>, then from
+    // the mean of what is left: where one candidate dominates, its ybar is
+    // close to <y, ybar>, and their difference would keep only the rounding.
+    dot = over_parts<Sp>(sh.x_dot, ln.row, add) * r;
+    float left = 0.0f;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        ybar[i] -= dot;
+        left = __builtin_fmaf(k[i], ybar[i], left);
+    }
+    sh.x_top[ln.part][ln.row] = left; // every part has read the maxima before the last barrier
+    if constexpr (Sp::kParts > 1) __syncthreads();
+    left = over_parts<Sp>(sh.x_top, ln.row, add) * r;
+    const float s = r * (a.inv_tau * a.inv_lambda);
+    f32x2v* out = reinterpret_cast<f32x2v*>(sh.tile + ln.row * Sp::C + ln.c0);
+#pragma unroll
+    for (int i = 0; i < K; i += 2) {
+        if (!ln.has(i)) continue;
+        out[i / 2] = f32x2v{(k[i] * s) * (ybar[i] - left), (k[i + 1] * s) * (ybar[i + 1] - left)};
+    }
+    __syncthreads();
+    if constexpr (kFull) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(sh.tile);
+        f32x4* dst = reinterpret_cast<f32x4*>(a.dalpha + base * Sp::C);
+        for (int i = threadIdx.x; i < Sp::kFloats / 4; i += Sp::kThreads)
+            stream_store(src[i], dst + i);
+    } else {
+        tile_out<Sp::kThreads>(sh.tile, a.dalpha + base * Sp::C, here * Sp::C);
+    }
+    __syncthreads(); // before the next block of groups overwrites the tile
+}
+
+template <int M, int N>
+__global__ __launch_bounds__((CatSplit<M, N>::kThreads), kSplitWaves) void cat_bwd_split_kernel(
+    CatArgs a)
+{
+    constexpr int G = CatSplit<M, N>::kGroups;
+    __shared__ CatBwdShared<M, N> sh;
+    for (int64_t base = (int64_t)blockIdx.x * G; base < a.ngroups; base += (int64_t)gridDim.x * G) {
+        if (base + G <= a.ngroups) // uniform over the block
+            cat_bwd_split_tile<M, N, true>(a, sh, base);
+        else
+            cat_bwd_split_tile<M, N, false>(a, sh, base);
+    }
+}
+
+template <int M, int N>
+void* pick_cat_fwd(bool soft)
+{
+    if constexpr (cat_split(Candidates<M, N>::C))
+        return soft ? (void*)cat_fwd_split_kernel<M, N, true>
+                    : (void*)cat_fwd_split_kernel<M, N, false>;
+    else
+        return soft ? (void*)cat_fwd_kernel<M, N, true> : (void*)cat_fwd_kernel<M, N, false>;
+}
+
+template <int M, int N>
+void* pick_cat_bwd()
+{
+    if constexpr (cat_split(Candidates<M, N>::C))
+        return (void*)cat_bwd_split_kernel<M, N>;
+    else
+        return (void*)cat_bwd_kernel<M, N>;
+}
+
 template <int M, int... Ns>
 void* cat_fwd_for_n(int n, bool soft, std::integer_sequence<int, Ns...>)
 {
     void* f = nullptr;
-    ((n == Ns + 1 ? (f = soft ? (void*)cat_fwd_kernel<M, Ns + 1, true>
-                              : (void*)cat_fwd_kernel<M, Ns + 1, false>,
-                     0)
-                  : 0),
-     ...);
+    ((n == Ns + 1 ? (f = pick_cat_fwd<M, Ns + 1>(soft), 0) : 0), ...);
     return f;
 }
 
@@ -475,7 +1011,7 @@ template <int M, int... Ns>
 void* cat_bwd_for_n(int n, std::integer_sequence<int, Ns...>)
 {
     void* f = nullptr;
-    ((n == Ns + 1 ? (f = (void*)cat_bwd_kernel<M, Ns + 1>, 0) : 0), ...);
+    ((n == Ns + 1 ? (f = pick_cat_bwd<M, Ns + 1>(), 0) : 0), ...);
     return f;
 }
 
@@ -525,9 +1061,12 @@ int cat_run(bool fwd, const uint16_t* W, const float* alpha, const uint16_t* G, 
     a.inv_lambda = (float)(1.0 / (double)lambda);
     a.inv_tau = (float)(1.0 / (double)tau);
     void* args[] = {&a};
-    const int block = cat_block(C);
-    if (hipLaunchKernel(fn, dim3(grid_for(ngroups, block)), dim3(block), args, 0, stream) !=
-        hipSuccess)
+    // groups and threads per block; a dispatch holds fewer than 2^32 threads
+    const int groups = cat_split(C) ? 64 * cat_rows(C) : kCatBlock;
+    const int threads = cat_split(C) ? groups * cat_parts(C) : kCatBlock;
+    const int64_t need = (ngroups + groups - 1) / groups;
+    const unsigned grid = (unsigned)std::min<int64_t>(need, 0xFFFFFFFFu / (unsigned)threads);
+    if (hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream) != hipSuccess)
         return launch_status(what);
     return launch_status(what);
 }

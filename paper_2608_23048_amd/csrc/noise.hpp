@@ -163,6 +163,11 @@ __device__ __forceinline__ void publish_log_table(float2* tab, float4 cells)
     __builtin_amdgcn_wave_barrier();
 }
 
+// Keeps the computation of v where it is written: the compiler would otherwise
+// sink the last steps of a logarithm past the wait for the loads that the
+// noise is meant to cover, to where the value is used.
+__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
+
 // ln of the float whose bit pattern is ix.  With t = ix - kLogZBaseBits the
 // exponent is k = floor(t / 2^23), z = x 2^-k and the cell is bits 16..22 of
 // t.  The code forms v = 0x7FFFFF - t instead: its low 23 bits are those of t

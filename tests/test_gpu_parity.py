@@ -760,7 +760,12 @@ CAT = [(37, 36, 2, 4, 1.0, 1.0, 0), (64, 96, 2, 4, 0.3, 0.6, 5), (33, 64, 1, 4, 
        (61, 88, 4, 8, 1.0, 2.0, 2 ** 33 + 5), (25, 64, 1, 8, 0.4, 1.0, 11),
        (25, 64, 7, 8, 1.0, 1.0, 0), (19, 96, 3, 8, 0.8, 1.0, 2 ** 40),
        # 8 candidates over several full 256-group chunks and a ragged one
-       (70, 64, 1, 8, 0.6, 1.0, 9), (67, 48, 7, 8, 1.0, 0.8, 2 ** 32 - 100)]
+       (70, 64, 1, 8, 0.6, 1.0, 9), (67, 48, 7, 8, 1.0, 0.8, 2 ** 32 - 100),
+       # 28 to 70 candidates, split over waves: several full blocks of 64 or 128
+       # groups and a ragged one, exactly one block, one group
+       (64, 72, 2, 8, 0.5, 1.0, 3), (43, 72, 3, 8, 0.5, 0.7, 1), (64, 64, 4, 8, 0.4, 1.0, 2),
+       (31, 72, 4, 8, 0.5, 1.0, 2 ** 33 - 77), (43, 72, 5, 8, 1.0, 1.0, 5),
+       (16, 64, 6, 8, 0.7, 1.0, 0), (1, 8, 4, 8, 1.0, 1.0, 4), (1, 8, 2, 8, 1.0, 0.6, 4)]
 
 
 def cat_fp32_floor(alpha, G_bits, W_bits, n, m, tau, lam, seed, step, goff):
@@ -870,7 +875,7 @@ def test_full_cat_7b_stack_2of4(dev):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("n,m", [(2, 4), (4, 8), (2, 8)])
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8), (2, 8), (3, 8), (5, 8)])
 def test_cat_ties_and_near_ties(dev, n, m):
     """Logits built from the oracle's noise so that candidate keys tie exactly
     or nearly: the choice must still be the exact keys' (lowest candidate on a
