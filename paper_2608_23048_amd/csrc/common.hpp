@@ -246,9 +246,12 @@ struct ExportArgs {
     uint8_t* idx;   // [groups, n] their indices, or NULL
     uint32_t* meta; // [ceil(groups / 8)] 2:4 index fields, or NULL
     int64_t ngroups;
+    int n; // kept per group (m > 8; a template argument of the other kernels)
 };
 using ExportFn = void (*)(ExportArgs);
 ExportFn select_export(int m, int n);
+// Groups one block (kBlock threads) of the export covers.
+int64_t export_block_groups(int m);
 
 // Kernels for m = 16 and 32 (wide_fwd.hip, wide_bwd.hip): four consecutive elements per lane,
 // a group spread over m / 4 adjacent lanes.

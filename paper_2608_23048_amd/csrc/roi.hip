@@ -1110,9 +1110,10 @@ extern "C" int roi_mask_export(const float* logits, const uint16_t* W, int64_t r
     if (int st = check_overlaps(ranges)) return st;
     ExportFn fn = select_export(m, n);
     if (!fn) return fail(ROI_E_UNSUPPORTED, "no kernel for %d:%d", n, m);
-    ExportArgs a{logits, W, W_masked, values, idx, meta, sh.ngroups};
+    ExportArgs a{logits, W, W_masked, values, idx, meta, sh.ngroups, n};
+    const int64_t blocks = ceil_div(sh.ngroups, export_block_groups(m));
     void* args[] = {&a};
-    if (hipLaunchKernel((const void*)fn, dim3(grid_for(sh.ngroups)), dim3(kBlock), args, 0,
+    if (hipLaunchKernel((const void*)fn, dim3(grid_for(blocks * kBlock)), dim3(kBlock), args, 0,
                         stream) != hipSuccess)
         return launch_status("roi_mask_export");
     return launch_status("roi_mask_export");

@@ -214,16 +214,46 @@ __device__ __forceinline__ float float_of_sortable_int(int v)
     return __int_as_float(sortable_int(__int_as_float(v)));
 }
 
+// Sorts a group's integers (four per lane, entry 4 part + e) in descending
+// order.  Every merge of KK entries starts by pairing i with i ^ (KK - 1),
+// after which all comparisons point the same way and every lane exchange is
+// one DPP permutation (xor 1, 2, 3 or 7).
+template <int M>
+__device__ __forceinline__ void sort_group(int (&p)[4], int part)
+{
+    static_assert(M == 8 || M == 16 || M == 32, "group size");
+    constexpr int kMax = 0x7FFFFFFF, kMin = -0x7FFFFFFF - 1;
+    const int b1 = (part & 1) == 0 ? kMax : kMin;
+    const int b2 = (part & 2) == 0 ? kMax : kMin;
+    const int b4 = (part & 4) == 0 ? kMax : kMin;
+    packed_stage<1>(p, 0);
+    packed_stage<3>(p, 0);
+    packed_stage<1>(p, 0);
+    packed_stage<7>(p, b1); // 8: lane xor 1
+    packed_stage<2>(p, 0);
+    packed_stage<1>(p, 0);
+    if constexpr (M >= 16) {
+        packed_stage<15>(p, b2); // 16: lane xor 3
+        packed_stage<4>(p, b1);
+        packed_stage<2>(p, 0);
+        packed_stage<1>(p, 0);
+    }
+    if constexpr (M == 32) {
+        packed_stage<31>(p, b4); // 32: lane xor 7
+        packed_stage<8>(p, b2);
+        packed_stage<4>(p, b1);
+        packed_stage<2>(p, 0);
+        packed_stage<1>(p, 0);
+    }
+}
+
 // Hard top-n by a bitonic sort of one 32-bit integer per key: the key's
 // order-preserving integer with its low log2(m) bits replaced by the entry's
 // index, so that an exchange is a minimum and a maximum (in a lane) or a DPP
-// move and a median (across lanes), and the index travels for free.  Every
-// merge of KK entries starts by pairing i with i ^ (KK - 1), after which all
-// comparisons point the same way and every lane exchange is one DPP
-// permutation (xor 1, 2, 3 or 7).  On MI355X the minimum, maximum, median and
-// DPP each issue in 4.2 cycles per wave: 16:32 over 1.31e9 weights sorts with
-// 350 issue cycles per wave instead of 940 with keys and indices carried
-// apart.
+// move and a median (across lanes), and the index travels for free.  On MI355X
+// the minimum, maximum, median and DPP each issue in 4.2 cycles per wave: 16:32
+// sorts with 350 issue cycles per wave instead of 940 with keys and indices
+// carried apart.
 //
 // Replacing the low bits moves a key by less than m ulps, m 2^-23 |K|.  The
 // result is decided -- the order of ranks 0 .. n-1 and the kept set are those
@@ -243,7 +273,6 @@ __device__ __forceinline__ bool wide_top_packed(const float (&kf)[4], int part, 
 {
     constexpr int M = 4 * L;
     constexpr int kIdx = M - 1;
-    constexpr int kMax = 0x7FFFFFFF, kMin = -0x7FFFFFFF - 1;
     int own[4], p[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -254,28 +283,7 @@ __device__ __forceinline__ bool wide_top_packed(const float (&kf)[4], int part, 
                                                   (uint32_t)(4 * part + e), 0xEA);
         p[e] = own[e];
     }
-    const int b1 = (part & 1) == 0 ? kMax : kMin;
-    const int b2 = (part & 2) == 0 ? kMax : kMin;
-    packed_stage<1>(p, 0);
-    packed_stage<3>(p, 0);
-    packed_stage<1>(p, 0);
-    packed_stage<7>(p, b1); // 8: lane xor 1
-    packed_stage<2>(p, 0);
-    packed_stage<1>(p, 0);
-    packed_stage<15>(p, b2); // 16: lane xor 3
-    packed_stage<4>(p, b1);
-    packed_stage<2>(p, 0);
-    packed_stage<1>(p, 0);
-    if constexpr (M == 32) {
-        const int b4 = (part & 4) == 0 ? kMax : kMin;
-        packed_stage<31>(p, b4); // 32: lane xor 7
-        packed_stage<8>(p, b2);
-        packed_stage<4>(p, b1);
-        packed_stage<2>(p, 0);
-        packed_stage<1>(p, 0);
-    } else {
-        static_assert(M == 16, "group size");
-    }
+    sort_group<M>(p, part);
     const int lane = (int)(threadIdx.x & 63);
     const int kth = __shfl(p[(N - 1) % 4], lane - part + (N - 1) / 4);
 #pragma unroll

@@ -725,6 +725,45 @@ def test_export_full_7b_stack(dev):
     torch.cuda.empty_cache()
 
 
+EXPORT_WIDE = [(m, n) for m in (16, 32) for n in (1, 3, 4, m // 2, m - 1, m)]
+
+
+@pytest.mark.parametrize("m,n", EXPORT_WIDE)
+def test_export_wide_edges(dev, m, n):
+    """The wide export over several blocks and a ragged one: ties at, above and
+    below the n-th logit, -0 beside +0, infinities and NaN.  Every form against
+    ranks counted by the sampler's rule, the earlier of two entries winning when
+    it is >= the later (so a comparison with NaN lets the later one win)."""
+    import torch
+    rows, cols = 83, 32 * 9
+    say(f"wide export {n}:{m}")
+    rng = np.random.default_rng(m + n)
+    L = np.round(rng.normal(0, 2, (rows * cols // m, m)) * 4).astype(np.float32) / 4
+    L[::3] = rng.normal(0, 1, L[::3].shape)
+    L[1::7, ::3] = -0.0
+    L[1::7, 1::3] = 0.0
+    L[2::11, : m // 2] = -np.inf
+    L[4::11, m // 3:] = np.inf
+    L[5::13, rng.integers(0, m)] = np.nan
+    G = L.shape[0]
+    beats = np.triu(L[:, :, None] >= L[:, None, :], 1)  # [g, i, j]: i < j and i beats j
+    lost = np.triu(~(L[:, :, None] >= L[:, None, :]), 1)  # i < j and j beats i
+    keep = beats.sum(1) + lost.sum(2) < n
+    W = torch.randn(rows, cols, generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
+    Wb = bf16_bits(W).reshape(G, m)
+    vals_o, idx_o = np.zeros((G, n), np.uint16), np.zeros((G, n), np.uint8)
+    for g in range(G):
+        at = np.flatnonzero(keep[g])[:n]
+        vals_o[g, :at.size], idx_o[g, :at.size] = Wb[g, at], at
+    Lt = torch.from_numpy(L.reshape(rows, cols)).to(dev)
+    Wm, vals, idx, _ = roi.mask_export(Lt, W.to(dev), n, m)
+    torch.cuda.synchronize()
+    assert np.array_equal(bf16_bits(Wm).reshape(G, m), np.where(keep, Wb, 0))
+    assert np.array_equal(bf16_bits(vals), vals_o) and np.array_equal(idx.cpu().numpy(), idx_o)
+    _, _, alone, _ = roi.mask_export(Lt, None, n, m, want_dense=False, want_values=False)
+    assert torch.equal(alone, idx)
+
+
 SPARSE_MM = [(16, 64, 16), (64, 256, 32), (48, 640, 48), (128, 3584, 32)]
 
 
