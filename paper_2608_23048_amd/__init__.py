@@ -128,9 +128,31 @@ def _raise_on(status: int):
                        lib().roi_status_string(status).decode())
 
 
-def _stream(t) -> int:
+# torch, once a call has needed it (the import statement in every call, and
+# torch.cuda.current_stream's Stream object, cost more than the arguments'
+# marshalling: a call on a small tensor took 7.6 us of host time with them, of
+# which 4.4 us are the library's launch, and takes 5.6 us without).
+_torch = None
+_raw_stream = None
+
+
+def _load_torch():
+    global _torch, _raw_stream
     import torch
-    return torch.cuda.current_stream(t.device).cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _raw_stream = raw or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+    _torch = torch
+    return torch
+
+
+def _stream(t) -> int:
+    """The handle of the current stream of t's device."""
+    if _torch is None:
+        _load_torch()
+    index = t.get_device()
+    if index < 0:
+        raise ValueError(f"expected a device tensor, got one on {t.device}")
+    return _raw_stream(index)
 
 
 def _ptr(t) -> int | None:
@@ -138,13 +160,17 @@ def _ptr(t) -> int | None:
 
 
 def _shape2d(t) -> tuple[int, int]:
-    if t.dim() == 2:
-        return int(t.shape[0]), int(t.shape[1])
-    return 1, int(t.numel())
+    shape = t.shape
+    if len(shape) == 2:
+        return shape[0], shape[1]
+    return 1, t.numel()
 
 
 def _check_tensor(t, dtype, name, like=None):
-    import torch
+    torch = _torch
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous()
+            and (like is None or t.shape == like.shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -153,8 +179,7 @@ def _check_tensor(t, dtype, name, like=None):
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if like is not None and t.shape != like.shape:
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(like.shape)}")
+    raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(like.shape)}")
 
 
 # --------------------------------------------------------------------------- tensor API
@@ -168,7 +193,7 @@ def mask_fwd(W, logits, n: int, m: int, tau: float = 1.0, lam: float = 1.0, seed
     soft_forward=False: straight-through forward, W_masked = W (.) hard mask;
     soft_forward=True: pure soft forward, W_masked = bf16(W (.) S).
     """
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(W, torch.bfloat16, "W")
     _check_tensor(logits, torch.float32, "logits", like=W)
     rows, cols = _shape2d(W)
@@ -192,7 +217,7 @@ def mask_fwd(W, logits, n: int, m: int, tau: float = 1.0, lam: float = 1.0, seed
 def mask_bwd(grad_W_masked, W, logits, n: int, m: int, tau: float = 1.0, lam: float = 1.0,
              seed: int = 0, step: int = 0, elem_offset: int = 0, out=None):
     """dL/dlogits (fp32, same shape as logits) from dL/dW_masked (bf16)."""
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(grad_W_masked, torch.bfloat16, "grad_W_masked")
     _check_tensor(W, torch.bfloat16, "W", like=grad_W_masked)
     _check_tensor(logits, torch.float32, "logits", like=grad_W_masked)
@@ -216,7 +241,7 @@ def mask_bwd_adamw(grad_W_masked, W, logits, exp_avg, exp_avg_sq, n: int, m: int
     """Backward with the AdamW step on the logits fused in: logits, exp_avg and
     exp_avg_sq (fp32, shaped like W) are updated in place; grad_out (fp32,
     optional) also receives dL/dlogits.  Returns grad_out."""
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(grad_W_masked, torch.bfloat16, "grad_W_masked")
     _check_tensor(W, torch.bfloat16, "W", like=grad_W_masked)
     for t, name in ((logits, "logits"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq")):
@@ -239,10 +264,10 @@ def mask_bwd_adamw_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float
     """mask_bwd_adamw over a list of (grad_W_masked, W, logits, exp_avg,
     exp_avg_sq) in one call (in place); grad_outs: optional list of fp32
     tensors receiving dL/dlogits."""
-    import torch
+    torch = _torch or _load_torch()
     if opt is None:
         raise ValueError("opt (AdamWParams) is required")
-    descs = []
+    fields = []
     offs = _offsets([W.numel() for _, W, *_ in tensors], offsets)
     for i, ((G, W, logits, ea, eas), off) in enumerate(zip(tensors, offs)):
         _check_tensor(G, torch.bfloat16, "grad_W_masked")
@@ -251,12 +276,11 @@ def mask_bwd_adamw_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float
             _check_tensor(t, torch.float32, name, like=G)
         d = grad_outs[i] if grad_outs is not None else None
         rows, cols = _shape2d(W)
-        descs.append(AdamWTensor(_ptr(G), _ptr(W), _ptr(logits), _ptr(ea), _ptr(eas), _ptr(d),
-                                 rows, cols, off))
-    arr = (AdamWTensor * max(1, len(descs)))(*descs)
+        fields += (_ptr(G), _ptr(W), _ptr(logits), _ptr(ea), _ptr(eas), _ptr(d), rows, cols, off)
+    arr = _descriptors(fields)  # roi_adamw_tensor
     stream = _stream(tensors[0][1]) if tensors else 0
-    _raise_on(lib().roi_mask_bwd_adamw_grouped(ctypes.addressof(arr), len(descs), n, m, tau, lam,
-                                               seed, step, ctypes.addressof(opt), stream))
+    _raise_on(lib().roi_mask_bwd_adamw_grouped(ctypes.addressof(arr), len(tensors), n, m, tau,
+                                               lam, seed, step, ctypes.addressof(opt), stream))
 
 
 def mask_export(logits, W, n: int, m: int, want_dense: bool = True, want_values: bool = True,
@@ -264,7 +288,7 @@ def mask_export(logits, W, n: int, m: int, want_dense: bool = True, want_values:
     """Final mask (top-n of the logits per group): returns (W_masked, values
     [G, n], idx [G, n] increasing, meta uint32 [ceil(G/8)] for 2:4), each
     None unless requested."""
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(logits, torch.float32, "logits")
     if W is not None:
         _check_tensor(W, torch.bfloat16, "W", like=logits)
@@ -286,7 +310,7 @@ def cat_num_candidates(n: int, m: int) -> int:
 
 
 def _check_cat(W, cat_logits, n, m):
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(W, torch.bfloat16, "W")
     _check_tensor(cat_logits, torch.float32, "cat_logits")
     C = cat_num_candidates(n, m)
@@ -303,7 +327,7 @@ def cat_mask_fwd(W, cat_logits, n: int, m: int, tau: float = 1.0, lam: float = 1
     """Categorical sampler forward (one logit per candidate mask, [G, C] fp32):
     returns (W_masked bf16, soft mask fp32 or None, chosen candidate uint8 [G]
     or None)."""
-    import torch
+    torch = _torch or _load_torch()
     _check_cat(W, cat_logits, n, m)
     rows, cols = _shape2d(W)
     out = out or {}
@@ -325,7 +349,7 @@ def cat_mask_fwd(W, cat_logits, n: int, m: int, tau: float = 1.0, lam: float = 1
 def cat_mask_bwd(grad_W_masked, W, cat_logits, n: int, m: int, tau: float = 1.0,
                  lam: float = 1.0, seed: int = 0, step: int = 0, group_offset: int = 0, out=None):
     """Categorical sampler backward: dL/dcat_logits (fp32, shaped like cat_logits)."""
-    import torch
+    torch = _torch or _load_torch()
     _check_cat(W, cat_logits, n, m)
     _check_tensor(grad_W_masked, torch.bfloat16, "grad_W_masked", like=W)
     rows, cols = _shape2d(W)
@@ -334,6 +358,12 @@ def cat_mask_bwd(grad_W_masked, W, cat_logits, n: int, m: int, tau: float = 1.0,
                                      n, m, tau, lam, seed, step, group_offset, _ptr(d),
                                      _stream(W)))
     return d
+
+
+def _descriptors(fields):
+    """The descriptors of a grouped call, every field of which is 8 bytes wide:
+    the fields of all of them in order, None for a NULL pointer."""
+    return (_u64 * max(1, len(fields)))(*[0 if f is None else f for f in fields])
 
 
 def _offsets(sizes, offsets):
@@ -355,8 +385,8 @@ def mask_fwd_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float = 1.0
     offsets default to the running sum of the sizes (a stack in list order).
     Returns a list of (W_masked, soft_mask or None, sel_idx or None); `outs`
     may hold such a list, preallocated."""
-    import torch
-    given, outs, descs = outs, [], []
+    torch = _torch or _load_torch()
+    given, outs, fields = outs, [], []
     offs = _offsets([W.numel() for W, _ in tensors], offsets)
     for i, ((W, logits), off) in enumerate(zip(tensors, offs)):
         _check_tensor(W, torch.bfloat16, "W")
@@ -372,12 +402,11 @@ def mask_fwd_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float = 1.0
             idx = (torch.empty((W.numel() // m if m > 0 else 0, n), dtype=torch.uint8,
                                device=W.device) if want_idx else None)
         outs.append((Wm, S, idx))
-        descs.append(FwdTensor(_ptr(W), _ptr(logits), _ptr(Wm), _ptr(S), _ptr(idx), rows, cols,
-                               off))
-    arr = (FwdTensor * max(1, len(descs)))(*descs)
+        fields += (_ptr(W), _ptr(logits), _ptr(Wm), _ptr(S), _ptr(idx), rows, cols, off)
+    arr = _descriptors(fields)  # roi_fwd_tensor
     fn = lib().roi_mask_fwd_soft_grouped if soft_forward else lib().roi_mask_fwd_grouped
     stream = _stream(tensors[0][0]) if tensors else 0
-    _raise_on(fn(ctypes.addressof(arr), len(descs), n, m, tau, lam, seed, step, stream))
+    _raise_on(fn(ctypes.addressof(arr), len(outs), n, m, tau, lam, seed, step, stream))
     return outs
 
 
@@ -385,8 +414,8 @@ def mask_bwd_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float = 1.0
                      step: int = 0, offsets=None, outs=None):
     """mask_bwd over a list of (grad_W_masked, W, logits) triples in one call;
     returns the list of grad_logits (`outs`: preallocated, optional)."""
-    import torch
-    given, outs, descs = outs, [], []
+    torch = _torch or _load_torch()
+    given, outs, fields = outs, [], []
     offs = _offsets([W.numel() for _, W, _ in tensors], offsets)
     for i, ((G, W, logits), off) in enumerate(zip(tensors, offs)):
         _check_tensor(G, torch.bfloat16, "grad_W_masked")
@@ -396,10 +425,10 @@ def mask_bwd_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float = 1.0
         d = given[i] if given is not None else torch.empty_like(logits)
         _check_tensor(d, torch.float32, "grad_logits", like=logits)
         outs.append(d)
-        descs.append(BwdTensor(_ptr(G), _ptr(W), _ptr(logits), _ptr(d), rows, cols, off))
-    arr = (BwdTensor * max(1, len(descs)))(*descs)
+        fields += (_ptr(G), _ptr(W), _ptr(logits), _ptr(d), rows, cols, off)
+    arr = _descriptors(fields)  # roi_bwd_tensor
     stream = _stream(tensors[0][1]) if tensors else 0
-    _raise_on(lib().roi_mask_bwd_grouped(ctypes.addressof(arr), len(descs), n, m, tau, lam, seed,
+    _raise_on(lib().roi_mask_bwd_grouped(ctypes.addressof(arr), len(outs), n, m, tau, lam, seed,
                                          step, stream))
     return outs
 
@@ -407,7 +436,7 @@ def mask_bwd_grouped(tensors, n: int, m: int, tau: float = 1.0, lam: float = 1.0
 def gumbel_noise(count: int, seed: int = 0, step: int = 0, elem_offset: int = 0, device="cuda",
                  want_words: bool = True, want_gumbel: bool = True):
     """Raw Philox words (as int32 bit patterns) and Gumbel noise of `count` elements."""
-    import torch
+    torch = _torch or _load_torch()
     words = torch.empty(count, dtype=torch.int32, device=device) if want_words else None
     g = torch.empty(count, dtype=torch.float32, device=device) if want_gumbel else None
     ref = words if words is not None else g
@@ -418,7 +447,7 @@ def gumbel_noise(count: int, seed: int = 0, step: int = 0, elem_offset: int = 0,
 
 def gumbel_from_words(words):
     """g = -L(-L(u(x))) for int32 tensors holding 32-bit words."""
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(words, torch.int32, "words")
     g = torch.empty(words.shape, dtype=torch.float32, device=words.device)
     _raise_on(lib().roi_gumbel_from_words(_ptr(words), words.numel(), _ptr(g), _stream(words)))
@@ -437,7 +466,7 @@ def stream_copy(src, dst):
 
 def fast_noise_from_words(words):
     """K = -log2(-log2 u(x)) from the hardware logarithm, for int32 word tensors."""
-    import torch
+    torch = _torch or _load_torch()
     _check_tensor(words, torch.int32, "words")
     out = torch.empty(words.shape, dtype=torch.float32, device=words.device)
     _raise_on(lib().roi_fast_noise_from_words(_ptr(words), words.numel(), _ptr(out),

@@ -364,3 +364,16 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(roi, "LIB_PATH", str(tmp_path / "missing.so"))
     with pytest.raises(RuntimeError, match="not built"):
         roi.lib()
+
+
+def test_host_tensors_are_refused_before_any_launch():
+    """Calls that check no tensor themselves take their stream from a tensor's
+    device, and refuse one on the host."""
+    import torch
+    a, b = torch.zeros(8), torch.zeros(8)
+    with pytest.raises(ValueError):
+        roi.stream_copy(a, b)
+    with pytest.raises(ValueError):
+        roi.gumbel_noise(8, device="cpu")
+    with pytest.raises(ValueError):
+        roi.mask_fwd(a.bfloat16(), b, 2, 4)
