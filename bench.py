@@ -34,7 +34,7 @@ VALU_FILE = os.path.join(ROOT, "profiles", "roi_mask_valu_counters.json")
 
 # The sources the benchmark's two kernels (fwd_lane_kernel, bwd_lane_kernel
 # for m = 4 and 8) are compiled from.
-KERNEL_SOURCES = ("roi.hip", "common.hpp", "noise.hpp", "relax.hpp", "host.hpp")
+KERNEL_SOURCES = ("roi.hip", "common.hpp", "noise.hpp", "quotient.hpp", "relax.hpp", "host.hpp")
 # ... and those of every straight-through forward and backward kernel (the
 # counter record covers the lane and the wide kernels).
 ALL_KERNEL_SOURCES = KERNEL_SOURCES + ("wide.hpp", "wide_fwd.hip", "wide_bwd.hip")

@@ -164,6 +164,7 @@ struct CatArgs {
     uint64_t group0;   // global index of group 0
     NoiseKey key;      // block_hi unused
     float lambda;
+    float div_y;       // 1 / lambda for quotients() (noise.hpp), or 0
     float key_c;       // fl(log2(e) / lambda)
     float inv_lambda;
     float inv_tau;
@@ -172,15 +173,17 @@ struct CatArgs {
 // The exact keys of one group (the words x come from its B Philox blocks).
 template <int C>
 __device__ __forceinline__ void cat_exact_keys(const float (&alpha)[C], const uint32_t (&x)[C],
-                                               float lambda, const float2* tab, float (&k)[C])
+                                               float lambda, float div_y, const float2* tab,
+                                               float (&k)[C])
 {
     // a wave-uniform branch, so that lambda = 1 does not run the division
     if (__builtin_amdgcn_readfirstlane(__float_as_uint(lambda)) == 0x3F800000u) {
 #pragma unroll
         for (int c = 0; c < C; ++c) k[c] = alpha[c] - neg_gumbel_from_word(x[c], tab);
     } else {
+        quotients<C>(alpha, lambda, div_y, k);
 #pragma unroll
-        for (int c = 0; c < C; ++c) k[c] = alpha[c] / lambda - neg_gumbel_from_word(x[c], tab);
+        for (int c = 0; c < C; ++c) k[c] -= neg_gumbel_from_word(x[c], tab);
     }
 }
 
@@ -276,7 +279,7 @@ __global__ __launch_bounds__(kCatBlock) void cat_fwd_kernel(CatArgs a)
             exact = C > 1 && !(top - second > margin);
         }
         if (exact) {
-            cat_exact_keys<C>(alpha, x, a.lambda, tab, k);
+            cat_exact_keys<C>(alpha, x, a.lambda, a.div_y, tab, k);
             float top = k[0];
             best = 0;
 #pragma unroll
@@ -324,14 +327,15 @@ __global__ __launch_bounds__(kCatBlock) void cat_fwd_kernel(CatArgs a)
 // without the division.
 template <int C>
 __device__ __forceinline__ void cat_keys_from_noise(const float (&alpha)[C], const float (&ng)[C],
-                                                    float lambda, float (&k)[C])
+                                                    float lambda, float div_y, float (&k)[C])
 {
     if (__builtin_amdgcn_readfirstlane(__float_as_uint(lambda)) == 0x3F800000u) {
 #pragma unroll
         for (int c = 0; c < C; ++c) k[c] = alpha[c] - ng[c];
     } else {
+        quotients<C>(alpha, lambda, div_y, k);
 #pragma unroll
-        for (int c = 0; c < C; ++c) k[c] = alpha[c] / lambda - ng[c];
+        for (int c = 0; c < C; ++c) k[c] -= ng[c];
     }
 }
 
@@ -397,7 +401,7 @@ __device__ __forceinline__ void cat_bwd_chunk(const CatArgs& a, float* tile, flo
     if (live) {
         // the keys the forward sampled, and their softmax
         float y[C];
-        cat_keys_from_noise<C>(alpha, ng, a.lambda, y);
+        cat_keys_from_noise<C>(alpha, ng, a.lambda, a.div_y, y);
         cat_softmax<C>(y, kLog2e * a.inv_tau);
         // Straight-through: dL/dS = dL/dW_masked (.) W; ybar_c = sum_{j in c} sbar_j.
         float sbar[M];
@@ -583,16 +587,20 @@ __device__ __forceinline__ void split_logits(const float* tile, const CatLane<Sp
 // the end are -inf (below every key, weight 0).
 template <typename Sp>
 __device__ __forceinline__ void split_keys(const CatLane<Sp>& ln, const float (&alpha)[Sp::K],
-                                           float lambda, float (&k)[Sp::K])
+                                           float lambda, float div_y, float (&k)[Sp::K])
 {
     if (__builtin_amdgcn_readfirstlane(__float_as_uint(lambda)) == 0x3F800000u) {
 #pragma unroll
         for (int i = 0; i < Sp::K; ++i) k[i] = alpha[i] - k[i];
     } else {
 #pragma unroll
-        for (int i = 0; i < Sp::K; ++i) {
-            k[i] = alpha[i] / lambda - k[i];
-            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0); // few quotients in the making
+        for (int i = 0; i < Sp::K; i += 4) {
+            const float a4[4] = {alpha[i], alpha[i + 1], alpha[i + 2], alpha[i + 3]};
+            float q4[4];
+            quotients<4>(a4, lambda, div_y, q4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k[i + e] = q4[e] - k[i + e];
+            __builtin_amdgcn_sched_barrier(0); // few quotients in the making
         }
     }
 #pragma unroll
@@ -777,7 +785,7 @@ __device__ __forceinline__ void cat_fwd_split_tile(const CatArgs& a, CatFwdShare
             split_noise<Sp>(again, ln.part, a.key, k, exact_noise);
             split_logits<Sp>(sh.tile, ln, alpha);
         }
-        split_keys<Sp>(ln, alpha, a.lambda, k);
+        split_keys<Sp>(ln, alpha, a.lambda, a.div_y, k);
         float top;
         lane_argmax<Sp>(ln, k, top, best);
         sh.x_top[ln.part][ln.row] = top;
@@ -895,7 +903,7 @@ __device__ __forceinline__ void cat_bwd_split_tile(const CatArgs& a, CatBwdShare
     {
         float alpha[K];
         split_logits<Sp>(sh.tile, ln, alpha);
-        split_keys<Sp>(ln, alpha, a.lambda, k);
+        split_keys<Sp>(ln, alpha, a.lambda, a.div_y, k);
     }
     float mx = k[0];
 #pragma unroll
@@ -1057,6 +1065,7 @@ int cat_run(bool fwd, const uint16_t* W, const float* alpha, const uint16_t* G, 
     a.group0 = group_offset;
     a.key = make_key(seed, step, 0);
     a.lambda = lambda;
+    a.div_y = quotient_reciprocal(lambda);
     a.key_c = (float)(1.4426950408889634 / (double)lambda);
     a.inv_lambda = (float)(1.0 / (double)lambda);
     a.inv_tau = (float)(1.0 / (double)tau);

@@ -45,6 +45,7 @@ struct FwdBatch {
     int count;
     NoiseKey key_base; // key_base.block_hi is replaced by the piece's
     float lambda;
+    float div_y; // 1 / lambda for quotients() (noise.hpp), or 0
     float key_c; // fl(log2(e) / lambda): the scale of the hardware-log keys
     float inv_tau;
     float key_scale; // fl(fl(log2(e)) * inv_tau): exact keys to softmax arguments in log2 units
@@ -70,6 +71,7 @@ struct BwdBatch {
     int count;
     NoiseKey key_base; // key_base.block_hi is replaced by the piece's
     float lambda;
+    float div_y; // as in FwdBatch
     float inv_lambda;
     float tau;
     float inv_tau;

@@ -44,6 +44,12 @@ int grid_for(int64_t items, int block)
     return (int)(need < 1 ? 1 : (need < max_blocks ? need : max_blocks));
 }
 
+// A reciprocal of a float has no 25-bit midpoint within 2^-53 of it, so
+// rounding it to double first does not change the float.
+float quotient_reciprocal(float lambda)
+{
+    return lambda >= kQuotientLo && lambda <= kQuotientHi ? (float)(1.0 / (double)lambda) : 0.0f;
+}
 
 NoiseKey make_key(uint64_t seed, uint64_t step, uint64_t block)
 {
@@ -198,10 +204,17 @@ __device__ __forceinline__ void group_words(uint32_t block, const NoiseKey& key,
 // The exact keys kappa = fl(fl(phi / lambda) + g) (noise.hpp).
 template <int M, bool kLambdaOne>
 __device__ __forceinline__ void exact_keys(const float (&phi)[M], const uint32_t (&x)[M],
-                                           float lambda, const float2* tab, float (&kappa)[M])
+                                           float lambda, float div_y, const float2* tab,
+                                           float (&kappa)[M])
 {
+    if constexpr (kLambdaOne) {
 #pragma unroll
-    for (int j = 0; j < M; ++j) kappa[j] = key_of<kLambdaOne>(phi[j], lambda, x[j], tab);
+        for (int j = 0; j < M; ++j) kappa[j] = phi[j] - neg_gumbel_from_word(x[j], tab);
+    } else {
+        quotients<M>(phi, lambda, div_y, kappa);
+#pragma unroll
+        for (int j = 0; j < M; ++j) kappa[j] -= neg_gumbel_from_word(x[j], tab);
+    }
 }
 
 // The hardware-log keys in log2 units (noise.hpp).
@@ -357,7 +370,7 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
                 } else {
                     float kappa[8];
                     int rank[8];
-                    exact_keys<8, kLambdaOne>(phi[u], x, a.lambda, tab, kappa);
+                    exact_keys<8, kLambdaOne>(phi[u], x, a.lambda, a.div_y, tab, kappa);
                     rank_keys<8>(kappa, rank);
                     store_masked<8>(pc.Wm + q * M, w[u], rank, N);
                     if (kWantIdx) store_idx<8, N>(pc.idx + q * N, rank);
@@ -367,14 +380,14 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
             float kappa[M];
             if constexpr (kRelax) {
                 // the relaxation's soft mask is an fp32 output: exact keys
-                exact_keys<M, kLambdaOne>(phi[u], x, a.lambda, tab, kappa);
+                exact_keys<M, kLambdaOne>(phi[u], x, a.lambda, a.div_y, tab, kappa);
             } else {
                 // Comparisons only: the hardware keys order every pair that is
                 // further apart than their error margin exactly as the exact keys
                 // do; a group with a closer pair (rare) takes the exact keys.
                 fast_keys<M>(phi[u], x, a.key_c, kappa);
                 if (!fast_keys_separated<M>(kappa))
-                    exact_keys<M, kLambdaOne>(phi[u], x, a.lambda, tab, kappa);
+                    exact_keys<M, kLambdaOne>(phi[u], x, a.lambda, a.div_y, tab, kappa);
             }
             const bool soft = kRelax && a.soft;
             if constexpr (kLaneTable) {
@@ -437,13 +450,13 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
 // Keys from the logits and the noise ng = -g of m elements (four at a time).
 template <int M>
 __device__ __forceinline__ void keys_from_noise(const float (&phi)[M], const float (&ng)[M],
-                                                float lambda, float (&kappa)[M])
+                                                float lambda, float div_y, float (&kappa)[M])
 {
 #pragma unroll
     for (int t = 0; t < M / 4; ++t) {
         const float p4[4] = {phi[4 * t], phi[4 * t + 1], phi[4 * t + 2], phi[4 * t + 3]};
         float a4[4];
-        scaled_logits4(p4, lambda, a4);
+        scaled_logits4(p4, lambda, div_y, a4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) kappa[4 * t + e] = a4[e] - ng[4 * t + e];
     }
@@ -487,7 +500,7 @@ __device__ __forceinline__ void soft_lane_chunk(const FwdBatch& a, const FwdPiec
         const int64_t q = base + u * kLaneBlock + threadIdx.x;
         if (!kFull && q >= ng_total) continue;
         float kappa[M];
-        keys_from_noise<M>(phi[u], ng[u], a.lambda, kappa);
+        keys_from_noise<M>(phi[u], ng[u], a.lambda, a.div_y, kappa);
         float S[M], b[M], bmax;
         StepRec<M> unused[N]; // not written when records are not kept
         if constexpr (kQ < 0) {
@@ -537,9 +550,10 @@ __device__ __forceinline__ void bwd_group4(const BwdBatch& a, const BwdPiece& pc
     constexpr int M = 4;
     float phi[M] = {in.phi.x, in.phi.y, in.phi.z, in.phi.w};
     // the keys the forward sampled: kappa = fl(fl(phi / lambda) + g) (noise.hpp)
-    float kappa[M];
+    float kappa[M] = {phi[0], phi[1], phi[2], phi[3]};
+    if constexpr (!kLambdaOne) quotients<M>(phi, a.lambda, a.div_y, kappa);
 #pragma unroll
-    for (int j = 0; j < M; ++j) kappa[j] = (kLambdaOne ? phi[j] : phi[j] / a.lambda) - ng[j];
+    for (int j = 0; j < M; ++j) kappa[j] -= ng[j];
     // Straight-through: dL/dS = dL/dW_masked (.) W, exact in fp32 (bf16 x bf16).
     const uint32_t w[M] = {in.w.x & 0xFFFFu, in.w.x >> 16, in.w.y & 0xFFFFu, in.w.y >> 16};
     const uint32_t g[M] = {in.g.x & 0xFFFFu, in.g.x >> 16, in.g.y & 0xFFFFu, in.g.y >> 16};
@@ -916,6 +930,7 @@ int mask_fwd_run(const char* what, bool soft, const roi_fwd_tensor* t, int count
     L.what = what;
     L.batch.key_base = make_key(seed, step, 0);
     L.batch.lambda = lambda;
+    L.batch.div_y = quotient_reciprocal(lambda);
     L.batch.key_c = (float)(1.4426950408889634 / (double)lambda); // log2(e) / lambda
     L.batch.inv_tau = (float)(1.0 / (double)tau);
     L.batch.key_scale = kLog2e * L.batch.inv_tau;
@@ -962,6 +977,7 @@ int mask_bwd_core(const char* what, const BwdDesc* t, int count, int n, int m, f
     L.what = what;
     L.batch.key_base = make_key(seed, step, 0);
     L.batch.lambda = lambda;
+    L.batch.div_y = quotient_reciprocal(lambda);
     L.batch.inv_lambda = (float)(1.0 / (double)lambda);
     L.batch.tau = tau;
     L.batch.inv_tau = (float)(1.0 / (double)tau);

@@ -442,12 +442,13 @@ __device__ __forceinline__ void wide_relax_backward(const StepRec<4> (&rec)[N],
 }
 
 __device__ __forceinline__ void wide_keys(const float (&phi)[4], uint32_t block, const NoiseKey& key,
-                                          float lambda, const float2* tab, float (&kappa)[4])
+                                          float lambda, float div_y, const float2* tab,
+                                          float (&kappa)[4])
 {
     const uint4 x = philox_block(block, key);
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
     float phi_bar[4];
-    scaled_logits4(phi, lambda, phi_bar);
+    scaled_logits4(phi, lambda, div_y, phi_bar);
 #pragma unroll
     for (int e = 0; e < 4; ++e) kappa[e] = phi_bar[e] - neg_gumbel_from_word(w[e], tab);
 }

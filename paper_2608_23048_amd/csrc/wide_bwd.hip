@@ -48,7 +48,7 @@ __device__ __forceinline__ void bwd_wide_slot(const BwdBatch& a, const BwdPiece&
     float phi[4] = {in.phi.x, in.phi.y, in.phi.z, in.phi.w};
     // the keys the forward sampled: kappa = fl(fl(phi / lambda) + g) (noise.hpp)
     float kappa[4];
-    scaled_logits4(phi, a.lambda, kappa);
+    scaled_logits4(phi, a.lambda, a.div_y, kappa);
 #pragma unroll
     for (int e = 0; e < 4; ++e) kappa[e] -= ng[e];
     // Straight-through: dL/dS = dL/dW_masked (.) W, exact in fp32.

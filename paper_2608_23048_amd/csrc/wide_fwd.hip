@@ -91,7 +91,7 @@ __device__ __forceinline__ void fwd_wide_span(const FwdBatch& a, const FwdPiece&
             decided = __all(wide_top_packed<L, N, false>(kf, part, keep, sidx));
         }
         if (!decided) {
-            wide_keys(phi, pc.block0 + (uint32_t)slot, key, a.lambda, tab, kappa);
+            wide_keys(phi, pc.block0 + (uint32_t)slot, key, a.lambda, a.div_y, tab, kappa);
             if (!kRelax || !__all(wide_top_packed<L, N, true>(kappa, part, keep, sidx)))
                 wide_top_ties<L, N>(kappa, part, keep, sidx);
         }
@@ -176,7 +176,7 @@ __device__ __forceinline__ void soft_wide_slot(const FwdBatch& a, const FwdPiece
     if (!kFull && slot >= nslots) return;
     const float phi[4] = {pv.x, pv.y, pv.z, pv.w};
     float kappa[4];
-    scaled_logits4(phi, a.lambda, kappa);
+    scaled_logits4(phi, a.lambda, a.div_y, kappa);
 #pragma unroll
     for (int e = 0; e < 4; ++e) kappa[e] -= ng[e];
     float S[4];

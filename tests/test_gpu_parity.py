@@ -305,6 +305,49 @@ def test_near_ties_bit_exact(dev, case):
         assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked differs ({want_soft})"
 
 
+DIVISION = [(n, m, lam) for n, m in ((2, 4), (2, 8), (8, 16), (16, 32))
+            for lam in (2.0 ** -21, 0.3, 3.0, 2.0 ** 21)]
+
+
+@pytest.mark.parametrize("n,m,lam", DIVISION)
+def test_logits_over_lambda(dev, n, m, lam):
+    """phi / lambda by residual corrections and, outside their range of lambda or
+    of phi (infinities, the type's lowest value), by division: near-tied keys,
+    so that a quotient off by one unit changes a selection, beside zeros and
+    huge logits.  Indices and masked weights are the oracle's, the soft mask and
+    the gradient within the tolerance where every logit is finite and tame."""
+    import torch
+    rows, cols, seed, step, tau = 48, 96, 3, 8, 0.8
+    groups = rows * cols // m
+    say(f"logits over lambda {n}:{m} lambda={lam}")
+    rng = np.random.default_rng(n * m)
+    g = oracle.keys(np.zeros(rows * cols, np.float32), 1.0, seed, step, 0).astype(np.float64)
+    steps = np.array([0.0, 1e-7, -1e-7, 4e-7, 1e-5, 0.5, -0.5])
+    target = rng.normal(0.0, 2.0, (groups, 1)) + rng.choice(steps, (groups, m))
+    L = ((target.reshape(-1) - g) * lam).astype(np.float32).reshape(groups, m)
+    tame = np.ones(groups, bool)
+    tame[: groups // 2] = False  # the first waves hold what must be divided
+    for q in range(0, groups // 2, 3):
+        L[q, rng.integers(0, m)] = rng.choice([np.inf, -np.inf, -3.4028235e38, 3e38, 0.0])
+    L = L.reshape(rows, cols)
+    W = (torch.randn(rows, cols, generator=torch.Generator().manual_seed(m)) + 6.0)
+    W, Lt = W.to(torch.bfloat16).to(dev), torch.from_numpy(L).to(dev)
+    G = torch.full((rows, cols), 1e-4, dtype=torch.bfloat16, device=dev)
+    G.view(-1)[::3] = -3e-4
+    Wm_o, S_o, idx_o = oracle.mask_fwd(bf16_bits(W), L, n, m, tau, lam, seed, step, 0)
+    d_o = oracle.mask_bwd(bf16_bits(G), bf16_bits(W), L, n, m, tau, lam, seed, step, 0)
+    for want_soft in (False, True):
+        Wm, S, idx = roi.mask_fwd(W, Lt, n, m, tau, lam, seed, step, 0, want_soft=want_soft)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), idx_o), f"indices differ (soft={want_soft})"
+        assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked differs ({want_soft})"
+    d = roi.mask_bwd(G, W, Lt, n, m, tau, lam, seed, step, 0)
+    torch.cuda.synchronize()
+    pick = lambda x: np.asarray(x).reshape(groups, m)[tame]
+    assert_close(pick(f32(S)), pick(S_o), "soft mask")
+    assert_close(pick(f32(d)), pick(d_o), "grad_logits", scale_aware=lam < 1.0)
+
+
 WIDE_SORT = [(n, m) for m in (16, 32) for n in (1, 3, 4, m // 2 + 1, m - 1, m)]
 
 
