@@ -388,6 +388,54 @@ def test_wide_sort_edges(dev, n, m):
         assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked (soft={want_soft})"
 
 
+HUGE = [(n, m, tau) for n, m in ((1, 4), (2, 4), (4, 4), (4, 8), (8, 16), (16, 32))
+        for tau in (1.0, 0.5, 0.7)]
+
+
+@pytest.mark.parametrize("n,m,tau", HUGE)
+def test_huge_common_keys(dev, n, m, tau):
+    """Groups whose logits share a huge value, as a masked row's do: the noise
+    disappears in it, the keys tie, S is n / m and the gradient is finite.  Then
+    keys a few units apart beside a huge common part, where the softmax's
+    arguments lose their differences if they are rounded before the shift.
+    S, dL/dlogits and the soft forward against the oracle; every third group
+    is an ordinary one, so that waves hold both.  Groups whose keys spread over
+    more than 31 in units of tau log(2) are left out: they take the log-domain
+    recursion, which rounds each key times log2(e) / tau by itself."""
+    import torch
+    rows, cols, seed, step = 24, 96, 4, 9
+    groups = rows * cols // m
+    say(f"huge common keys {n}:{m} tau={tau}")
+    tau32 = float(np.float32(tau))
+    rng = np.random.default_rng(m + n)
+    for common in (-1e4, -1e10, -1e30, 1e12, -3.4028235e38, 3e5, 2.0 ** 25):
+        L = np.full((groups, m), common, np.float32)
+        if common in (3e5, 2.0 ** 25):
+            L += 4.0 * rng.integers(-1, 2, (groups, m)).astype(np.float32)
+        L[::3] = rng.normal(0, 1, L[::3].shape)
+        L = L.reshape(rows, cols)
+        W = torch.from_numpy(rng.standard_normal((rows, cols)).astype(np.float32)).bfloat16()
+        G = torch.from_numpy(1e-3 * rng.standard_normal((rows, cols)).astype(np.float32)).bfloat16()
+        W, G, Lt = W.to(dev), G.to(dev), torch.from_numpy(L).to(dev)
+        Wm_o, S_o, idx_o = oracle.mask_fwd(bf16_bits(W), L, n, m, tau32, 1.0, seed, step, 0)
+        d_o = oracle.mask_bwd(bf16_bits(G), bf16_bits(W), L, n, m, tau32, 1.0, seed, step, 0)
+        Wm, S, idx = roi.mask_fwd(W, Lt, n, m, tau, 1.0, seed, step, 0, want_soft=True)
+        Ws, _, _ = roi.mask_fwd(W, Lt, n, m, tau, 1.0, seed, step, 0, want_idx=False,
+                                soft_forward=True)
+        d = roi.mask_bwd(G, W, Lt, n, m, tau, 1.0, seed, step, 0)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), idx_o), f"indices differ ({common})"
+        assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked differs ({common})"
+        kappa = oracle.keys(L.reshape(-1), 1.0, seed, step, 0).reshape(groups, m)
+        near = (kappa.max(axis=1) - kappa.min(axis=1)) * LOG2E / tau < 31.0
+        near |= np.arange(groups) % 3 == 0
+        assert near.mean() > 0.35  # beyond the ordinary third
+        pick = lambda x: np.asarray(x).reshape(groups, m)[near]
+        assert_close(pick(f32(S)), pick(S_o), f"soft mask ({common})")
+        assert_close(pick(f32(d)), pick(d_o), f"grad_logits ({common})")
+        soft_product_exact(bf16_bits(W), f32(S), bf16_bits(Ws), f"soft forward ({common})")
+
+
 # --------------------------------------------------------------------------- layout properties
 @pytest.mark.parametrize("tau", [1.0, 0.5, 0.4])
 def test_split_calls_equal_one_slab_call(dev, tau):
