@@ -678,12 +678,14 @@ __device__ __forceinline__ int best_of_parts(const float (*top)[Sp::kGroups],
     return b;
 }
 
-// The lane's largest key, ties to the lower candidate.
+// The lane's largest key, ties to the lower candidate.  A NaN never wins, as in
+// a scan over the group's candidates in order, where only candidate 0 can hold
+// the lead with one: a later part that starts with a NaN starts below every key.
 template <typename Sp>
 __device__ __forceinline__ void lane_argmax(const CatLane<Sp>& ln, const float (&k)[Sp::K],
                                             float& top, int& best)
 {
-    top = k[0];
+    top = ln.part > 0 && k[0] != k[0] ? -INFINITY : k[0];
     best = 0;
 #pragma unroll
     for (int i = 1; i < Sp::K; ++i) {

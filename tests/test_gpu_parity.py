@@ -1038,6 +1038,48 @@ def test_cat_ties_and_near_ties(dev, n, m):
     assert np.array_equal(bf16_bits(Wm_s).reshape(-1), Wm_o)
 
 
+@pytest.mark.parametrize("n,m", [(2, 4), (1, 8), (2, 8), (3, 8), (4, 8), (5, 8), (6, 8)])
+def test_cat_nan_and_infinite_logits(dev, n, m):
+    """A NaN key never wins, except that of candidate 0, which nothing beats;
+    among infinite keys the lower candidate wins.  NaN at the first candidates
+    of the group and of the waves that share it (24, 28 and 48), in their
+    middle, several at once, and groups of infinities: choices and masked
+    weights are the oracle's with and without S, and S is a number exactly
+    where the oracle's is."""
+    import torch
+    rows, cols = 41, 64
+    Gn = rows * cols // m
+    C = roi.cat_num_candidates(n, m)
+    say(f"cat NaN and infinities {n}:{m}")
+    rng = np.random.default_rng(C)
+    A = rng.standard_normal((Gn, C)).astype(np.float32)
+    places = [c for c in (0, 1, 3, 11, 23, 24, 25, 27, 28, 29, 40, 47, 48, 49, 60, C - 1) if c < C]
+    for i, c in enumerate(places):  # ordinary groups beside each
+        A[3 * i, c] = np.nan
+        A[3 * i + 1] = 0.0
+        A[3 * i + 1, c] = np.nan
+    for q in range(60, Gn - 20, 7):
+        A[q, rng.integers(0, C, 1 + q % 5)] = np.nan
+        A[q + 1, rng.integers(0, C, 1 + q % 3)] = np.inf
+        A[q + 2] = -np.inf
+        A[q + 2, rng.integers(0, C, 2)] = (np.nan, 1.0)
+        A[q + 3, rng.integers(0, C, C // 2)] = -np.inf
+    W = (torch.randn(rows, cols, generator=torch.Generator().manual_seed(2)) + 3).to(torch.bfloat16)
+    W, At = W.to(dev), torch.from_numpy(A).to(dev)
+    Wm_o, S_o, ch_o = oracle.cat_fwd(bf16_bits(W), A, n, m, 1.0, 1.0, 6, 2, 0)
+    for want_soft in (False, True):
+        Wm, S, ch = roi.cat_mask_fwd(W, At, n, m, 1.0, 1.0, 6, 2, 0, want_soft=want_soft)
+        torch.cuda.synchronize()
+        bad = np.flatnonzero(ch.cpu().numpy() != ch_o)
+        assert bad.size == 0, f"choices differ at {bad[:5]} (soft={want_soft})"
+        assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o)
+    S = f32(S).reshape(-1)
+    S_o = np.asarray(S_o).reshape(-1)
+    number = np.isfinite(S_o)
+    assert np.array_equal(np.isfinite(S), number)
+    assert_close(S[number], S_o[number], "categorical soft mask")
+
+
 def test_every_output_written_and_deterministic(dev):
     import torch
     W, L, G = wl.small_case(333, 64, 1, device=dev)
