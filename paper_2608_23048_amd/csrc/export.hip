@@ -140,15 +140,17 @@ __global__ __launch_bounds__(kBlock) void export_kernel(ExportArgs a)
 // wide kernels.
 //
 // The n-th largest logit of each group comes from a sort of order-preserving
-// integers (wide.hpp); the kept entries are those at or above it.  Groups in
-// which the n-th and the next logit tie, or that hold a NaN, are rare: their
-// wave counts, for every entry, the entries that beat it (rank_keys' rule).
+// integers (wide.hpp); the kept entries are those at or above it.  Where the
+// n-th and the next logit tie (logits that were never trained, for one), the
+// entries equal to it are kept in index order while there is room.  A wave with
+// a NaN counts, for every entry, the entries that beat it (rank_keys' rule).
 // The kept values and indices of a block are gathered in LDS and leave as
 // contiguous 16-byte stores.  One lane per group instead reads and writes at
 // strides of a whole group, its compressed outputs 1 or 2 bytes at a time, and
 // compares all pairs.  1.5B-class layer (46.8e6 weights), values and indices:
-// 16:32 208 us one lane per group, 66 us so; 8:16 127 and 62 us; 1:16 77 and
-// 60 us (54 us at the streaming-copy rate for 16:32).  At m = 8 the lane kernel
+// 16:32 207 us one lane per group, 71 us so; 8:16 126 and 65 us; 1:16 79 and
+// 68 us (54 us at the streaming-copy rate for 16:32); with every logit equal,
+// 16:32 172 and 71 us, 8:16 102 and 69 us, 1:16 65 and 66 us.  At m = 8 the lane kernel
 // stays: its group is 32 bytes, and it was faster, 4:8 57 and 63 us, 1:8 51 and
 // 58 us.
 template <int L>
@@ -216,13 +218,27 @@ __global__ __launch_bounds__(kBlock) void export_wide_kernel(ExportArgs a)
             sort_group<M>(p, part);
             const int first = lane - part; // the group's first lane
             const int kth = __shfl(pick4(p, n - 1), first + (n - 1) / 4);
-            bool undecided = __shfl(pick4(p, n), first + n / 4) == kth;
+            const bool tied = __shfl(pick4(p, n), first + n / 4) == kth;
             const float sum = (phi[0] + phi[1]) + (phi[2] + phi[3]);
-            undecided |= !(sum == sum); // a NaN (or opposite infinities)
             nib = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) nib |= own[e] >= kth ? 1u << e : 0u;
-            if (__any(undecided)) {
+            if (__any(tied)) {
+                uint32_t above = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) above |= own[e] > kth ? 1u << e : 0u;
+                const int room = n - __popc(group_or<L>(above << (4 * part)));
+                const uint32_t equal = group_or<L>((nib ^ above) << (4 * part));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t before = equal & ((1u << (4 * part + e)) - 1u);
+                    if (__popc(before) >= room) nib &= ~(1u << e) | above;
+                }
+            }
+            // the sum is NaN for opposite infinities too: look again, at each logit
+            if (__any(!(sum == sum)) &&
+                __any(phi[0] != phi[0] || phi[1] != phi[1] || phi[2] != phi[2] ||
+                      phi[3] != phi[3])) {
                 // Kept out of the common path's way: a rolled loop, its lane number
                 // hidden so that nothing of it is computed ahead of the branch.
                 int at = part;

@@ -855,6 +855,28 @@ def test_export_wide_edges(dev, m, n):
     assert torch.equal(alone, idx)
 
 
+@pytest.mark.parametrize("m,n", EXPORT_WIDE)
+def test_export_wide_equal_logits(dev, m, n):
+    """Whole waves of ties at the n-th logit: every logit equal, two levels,
+    and a tie among infinities of both signs.  The entries equal to the n-th
+    logit are kept from the lowest index, as the oracle keeps them."""
+    import torch
+    rows, cols = 45, 32 * 7
+    say(f"wide export of equal logits {n}:{m}")
+    rng = np.random.default_rng(m * 100 + n)
+    W = torch.randn(rows, cols, generator=torch.Generator().manual_seed(5)).to(torch.bfloat16)
+    levels = {"zero": [0.0], "signed zero": [0.0, -0.0], "two": [0.5, -1e30],
+              "infinities": [np.inf, -np.inf], "one level and the rest": [2.0, 1.0, 0.5, 0.25]}
+    for name, values in levels.items():
+        L = rng.choice(np.array(values, np.float32), (rows, cols)).astype(np.float32)
+        Wm_o, vals_o, idx_o, _ = oracle.export(L, bf16_bits(W), n, m)
+        Wm, vals, idx, _ = roi.mask_export(torch.from_numpy(L).to(dev), W.to(dev), n, m)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy().reshape(-1), np.asarray(idx_o).reshape(-1)), name
+        assert np.array_equal(bf16_bits(vals).reshape(-1), np.asarray(vals_o).reshape(-1)), name
+        assert np.array_equal(bf16_bits(Wm).reshape(-1), np.asarray(Wm_o).reshape(-1)), name
+
+
 SPARSE_MM = [(16, 64, 16), (64, 256, 32), (48, 640, 48), (128, 3584, 32)]
 
 
