@@ -110,15 +110,6 @@ struct StepRec {
     float om[M]; // 1 - mu^(k), evaluated as the sum of the other entries over the total
 };
 
-template <int M>
-__device__ __forceinline__ float largest_key(const float (&kappa)[M])
-{
-    float kmax = kappa[0];
-#pragma unroll
-    for (int j = 1; j < M; ++j) kmax = fmaxf(kmax, kappa[j]);
-    return kmax;
-}
-
 // Keys scaled for the relaxation: b_j = kappa_j * key_scale, the softmax
 // argument alpha / tau in log2 units; bmax = max b.  Returns the span
 // (max - min) of b.  key_scale is log2(e) / tau for keys in natural units and
@@ -131,11 +122,12 @@ template <int M, bool kSpan = true>
 __device__ __forceinline__ float scaled_keys(const float (&kappa)[M], float key_scale, float (&b)[M],
                                              float& bmax)
 {
-    const float kmax = largest_key<M>(kappa);
-    float kmin = kappa[0];
+    float kmax = kappa[0], kmin = kappa[0];
 #pragma unroll
-    for (int j = 1; j < M; ++j)
+    for (int j = 1; j < M; ++j) {
+        kmax = fmaxf(kmax, kappa[j]);
         if (kSpan) kmin = fminf(kmin, kappa[j]);
+    }
 #pragma unroll
     for (int j = 0; j < M; ++j) b[j] = kappa[j] * key_scale;
     bmax = kmax * key_scale; // = max b (rounding is monotone)
@@ -214,32 +206,32 @@ __device__ __forceinline__ void relax_forward(float (&b)[M], float bmax0, float 
 // multiply-add, carries a rounding of about 2^-24 of itself (and that of
 // key_scale), a relative error of about 4e-8 span in e_j.  span <=
 // kExpSpanAccuracy keeps it near 1e-6.  All of them also carry the rounding of
-// bmax, up to ulp(bmax) / 2, which cancels in the softmax while it is small:
-// at most 1 up to kFusedShiftMax.  Keys of 1e10 that tie (a mask's value in a
-// whole group) would overflow; such a group takes the log-domain loop, with
-// its keys shifted first (shift_huge_keys).
+// bmax, which cancels in the softmax while it is small (first_exps).
 constexpr float kExpNormalBound = 91.0f;
 constexpr float kExpSpanAccuracy = 32.0f;
+
+// The first step's exponentials, exp2((kappa_j - kmax) key_scale).  The fused
+// form shifts by bmax, the rounded kmax key_scale; its rounding, up to ulp(bmax)
+// / 2, is at most 1 up to kFusedShiftMax.  Keys of 1e10 that tie (a mask's value
+// in a whole group) would overflow, so beyond it the keys are shifted before
+// they are scaled: exactly, where they are close.  The branch is the wave's:
+// waves without such a group pay one comparison, and no selects.
 constexpr float kFusedShiftMax = 0x1p24f;
 
-// Whether a group takes the exp-domain form; exp_span is the host's limit.
-__device__ __forceinline__ bool takes_exp_form(float span, float exp_span, float bmax)
+template <int K, typename Max>
+__device__ __forceinline__ void first_exps(const float (&kappa)[K], float key_scale, float bmax,
+                                           Max group_kmax, float (&e)[K])
 {
-    return span <= exp_span && fabsf(bmax) <= kFusedShiftMax;
-}
-
-// Keys beyond the exp-domain form's range, shifted by the largest before they
-// are scaled: exactly, where they are close.  The branch is the wave's, so that
-// other waves pay one comparison and not the selects.
-template <int K>
-__device__ __forceinline__ void shift_huge_keys(const float (&kappa)[K], float kmax,
-                                                float key_scale, float (&b)[K], float& bmax)
-{
-    const bool huge = fabsf(bmax) > kFusedShiftMax;
-    if (!__any(huge)) return;
 #pragma unroll
-    for (int j = 0; j < K; ++j) b[j] = huge ? (kappa[j] - kmax) * key_scale : b[j];
-    bmax = huge ? 0.0f : bmax;
+    for (int j = 0; j < K; ++j)
+        e[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[j], key_scale, -bmax));
+    if (__any(fabsf(bmax) > kFusedShiftMax)) {
+        const bool huge = fabsf(bmax) > kFusedShiftMax;
+        const float kmax = group_kmax();
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            e[j] = huge ? __builtin_amdgcn_exp2f((kappa[j] - kmax) * key_scale) : e[j];
+    }
 }
 
 template <int kQ>
@@ -257,11 +249,16 @@ __device__ __forceinline__ void relax_forward_exp(const float (&kappa)[M], float
 {
     static_assert(kQ >= 0 && kQ <= 2, "exp-domain recursion: kQ");
     float e[M];
+    const auto largest = [&] {
+        float kmax = kappa[0];
 #pragma unroll
-    for (int j = 0; j < M; ++j) {
-        e[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[j], key_scale, -bmax));
+        for (int j = 1; j < M; ++j) kmax = fmaxf(kmax, kappa[j]);
+        return kmax;
+    };
+    first_exps<M>(kappa, key_scale, bmax, largest, e);
+#pragma unroll
+    for (int j = 0; j < M; ++j)
         if (kWantS) S[j] = 0.0f;
-    }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         float others[M], total;

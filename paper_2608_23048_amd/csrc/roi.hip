@@ -423,13 +423,11 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
                 float S[M], b[M], bmax;
                 StepRec<M> unused[N]; // not written when records are not kept
                 const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-                if (takes_exp_form(span, a.exp_span, bmax)) {
+                if (span <= a.exp_span)
                     relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
                                                      unused);
-                } else {
-                    shift_huge_keys<M>(kappa, largest_key<M>(kappa), a.key_scale, b, bmax);
+                else
                     relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
-                }
                 if (pc.S) {
                     f32x4* s4 = reinterpret_cast<f32x4*>(pc.S + q * M);
 #pragma unroll
@@ -508,15 +506,11 @@ __device__ __forceinline__ void soft_lane_chunk(const FwdBatch& a, const FwdPiec
         if constexpr (kQ < 0) {
             scaled_keys<M, false>(kappa, a.key_scale, b, bmax);
             relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
+        } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
+            relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
+                                                     unused);
         } else {
-            const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-            if (takes_exp_form(span, a.exp_span, bmax)) {
-                relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
-                                                         unused);
-            } else {
-                shift_huge_keys<M>(kappa, largest_key<M>(kappa), a.key_scale, b, bmax);
-                relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
-            }
+            relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
         }
         store_soft_product<M>(pc.Wm + q * M, w[u], S);
     }
@@ -576,17 +570,13 @@ __device__ __forceinline__ void bwd_group4(const BwdBatch& a, const BwdPiece& pc
         scaled_keys<M, false>(kappa, a.key_scale, b, bmax);
         relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
         relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
+    } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
+        relax_forward_exp<M, N, false, true, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S_unused,
+                                                  rec);
+        relax_backward<M, N, kQ == 1, false>(rec, sbar, a.inv_tau, abar);
     } else {
-        const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-        if (takes_exp_form(span, a.exp_span, bmax)) {
-            relax_forward_exp<M, N, false, true, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S_unused,
-                                                     rec);
-            relax_backward<M, N, kQ == 1, false>(rec, sbar, a.inv_tau, abar);
-        } else {
-            shift_huge_keys<M>(kappa, largest_key<M>(kappa), a.key_scale, b, bmax);
-            relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
-            relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
-        }
+        relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
+        relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
     }
     float grad[M]; // dL/dphi = dL/dkappa / lambda
 #pragma unroll

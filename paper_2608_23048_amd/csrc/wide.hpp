@@ -321,8 +321,7 @@ __device__ __forceinline__ bool wide_top_packed(const float (&kf)[4], int part, 
 
 // Relaxation over the group (§3.2 recursion, Algorithm 1), four entries per
 // lane: the exp-domain recursion of relax_forward_exp when the group's key
-// span is at most exp_span (the host's bound, relax.hpp) and its keys are not
-// huge, else the log-domain
+// span is at most exp_span (the host's bound, relax.hpp), else the log-domain
 // loop of relax_forward, with sums over the group's other lanes.  The choice
 // is the group's own (all its lanes agree), so its outputs do not depend on
 // which groups share its wave.  Returns true when this group took the
@@ -336,7 +335,7 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
     // (see scaled_keys in relax.hpp)
     const float kmax = group_max<L>(max4(kappa));
     const float c = key_scale;
-    float bmax0 = kmax * c;
+    const float bmax0 = kmax * c;
     float b[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -345,11 +344,9 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
     }
     // kQ < 0: the exp-domain form is off at this temperature (no span needed)
     const float span = kQ < 0 ? 0.0f : (kmax - group_min<L>(min4(kappa))) * c;
-    if (kQ >= 0 && takes_exp_form(span, exp_span, bmax0)) { // the same on all lanes of the group
+    if (kQ >= 0 && span <= exp_span) { // the same on all lanes of the group
         float ex[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            ex[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[e], c, -bmax0));
+        first_exps<4>(kappa, c, bmax0, [&] { return group_max<L>(max4(kappa)); }, ex);
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             float others[4], t;
@@ -371,7 +368,6 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
         }
         return true;
     }
-    if (kQ >= 0) shift_huge_keys<4>(kappa, kmax, c, b, bmax0);
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         float ex[4];
