@@ -153,16 +153,8 @@ __global__ __launch_bounds__(kBlock) void export_kernel(ExportArgs a)
 // 16:32 172 and 71 us, 8:16 102 and 69 us, 1:16 65 and 66 us.  At m = 8 the lane kernel
 // stays: its group is 32 bytes, and it was faster, 4:8 57 and 63 us, 1:8 51 and
 // 58 us.
-template <int L>
-__device__ __forceinline__ uint32_t group_or(uint32_t v)
-{
-    const auto bits = [](float f) { return __float_as_uint(f); };
-    v |= bits(lane_xor<1>(__uint_as_float(v)));
-    if constexpr (L >= 4) v |= bits(lane_xor<2>(__uint_as_float(v)));
-    if constexpr (L >= 8) v |= bits(other_quad(__uint_as_float(v)));
-    return v;
-}
 
+// p[i], without indexing registers.
 __device__ __forceinline__ int pick4(const int (&p)[4], int i)
 {
     const int a = i & 1 ? p[1] : p[0], b = i & 1 ? p[3] : p[2];

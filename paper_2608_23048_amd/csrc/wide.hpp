@@ -82,6 +82,17 @@ __device__ __forceinline__ float group_min(float v)
     return v;
 }
 
+// The OR of a value over the group.
+template <int L>
+__device__ __forceinline__ uint32_t group_or(uint32_t v)
+{
+    const auto bits = [](float f) { return __float_as_uint(f); };
+    v |= bits(lane_xor<1>(__uint_as_float(v)));
+    if constexpr (L >= 4) v |= bits(lane_xor<2>(__uint_as_float(v)));
+    if constexpr (L >= 8) v |= bits(other_quad(__uint_as_float(v)));
+    return v;
+}
+
 __device__ __forceinline__ float min4(const float (&x)[4])
 {
     return fminf(fminf(x[0], x[1]), fminf(x[2], x[3]));
@@ -317,6 +328,34 @@ __device__ __forceinline__ bool wide_top_packed(const float (&kf)[4], int part, 
         for (int e = 0; e < 4; ++e) sep &= unchecked(e) | (k[e] - k[e + 1] > margin);
     }
     return sep;
+}
+
+// After wide_top_packed left some group of the wave undecided (sep: its result):
+// groups whose keys are all equal, as a masked row's are where the mask's value
+// swallows the noise, keep their first n entries.  Returns whether every group
+// of the wave is decided now.  Over 46.8e6 weights of equal keys on MI355X,
+// forward with S at tau = 1, keys and indices sorted apart at once, after the
+// packed sort, and so: 16:32 210, 236 and 194 us, 8:16 153, 171 and 152 us, 1:16
+// 126, 145 and 123 us.  A check of the whole keys in sorted order, which would
+// also decide ties among some of a group's entries, made untied waves 7% slower.
+// So a group with fewer than n unmasked entries still sorts twice: 16:32 354 and
+// 383 us, 8:16 197 and 217 us.
+template <int L, int N>
+__device__ __forceinline__ bool wide_top_equal(const float (&kappa)[4], int part, bool sep,
+                                               bool (&keep)[4], int (&sidx)[4])
+{
+    const float first = __shfl(kappa[0], (int)(threadIdx.x & 63) - part);
+    const bool same = (kappa[0] == first) & (kappa[1] == first) & (kappa[2] == first) &
+                      (kappa[3] == first);
+    const uint32_t flags = group_or<L>((sep ? 0u : 1u) | (same ? 0u : 2u));
+    if (!__all(flags != 3u)) return false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4 * part + e;
+        keep[e] = flags & 2u ? keep[e] : i < N;
+        sidx[e] = flags & 2u ? sidx[e] : i;
+    }
+    return true;
 }
 
 // Relaxation over the group (§3.2 recursion, Algorithm 1), four entries per

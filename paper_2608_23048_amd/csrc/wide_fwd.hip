@@ -92,8 +92,11 @@ __device__ __forceinline__ void fwd_wide_span(const FwdBatch& a, const FwdPiece&
         }
         if (!decided) {
             wide_keys(phi, pc.block0 + (uint32_t)slot, key, a.lambda, a.div_y, tab, kappa);
-            if (!kRelax || !__all(wide_top_packed<L, N, true>(kappa, part, keep, sidx)))
-                wide_top_ties<L, N>(kappa, part, keep, sidx);
+            if constexpr (kRelax) {
+                const bool sep = wide_top_packed<L, N, true>(kappa, part, keep, sidx);
+                decided = __all(sep) || wide_top_equal<L, N>(kappa, part, sep, keep, sidx);
+            }
+            if (!decided) wide_top_ties<L, N>(kappa, part, keep, sidx);
         }
         const bool soft = kRelax && a.soft;
         if (!soft) store_wide_mask<N>(pc, slot, wv[u], keep);

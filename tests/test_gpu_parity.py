@@ -436,6 +436,42 @@ def test_huge_common_keys(dev, n, m, tau):
         soft_product_exact(bf16_bits(W), f32(S), bf16_bits(Ws), f"soft forward ({common})")
 
 
+@pytest.mark.parametrize("n,m", WIDE_SORT)
+def test_wide_equal_groups(dev, n, m):
+    """The wide forward with S where keys of a group are all equal: every group
+    of a wave, some of them beside ordinary ones, beside one near tie (so that
+    the wave sorts anew), all but one entry, equal keys of +-inf and of +-0.
+    Indices and masked weights are the oracle's."""
+    import torch
+    rows, cols, seed, step = 40, 96, 8, 3
+    groups = rows * cols // m
+    say(f"wide equal groups {n}:{m}")
+    rng = np.random.default_rng(n + m)
+    g = oracle.keys(np.zeros(rows * cols, np.float32), 1.0, seed, step, 0).reshape(groups, m)
+    W = torch.randn(rows, cols, generator=torch.Generator().manual_seed(n)) + 5.0
+    W = W.to(torch.bfloat16).to(dev)
+    for value in (-1e30, np.inf, -np.inf, 0.0):
+        L = rng.normal(0.0, 1.0, (groups, m)).astype(np.float32)
+        equal = np.full((groups, m), value, np.float32) if value else -g  # keys of +0
+        L[: groups // 4] = equal[: groups // 4]
+        L[groups // 4 : groups // 2 : 3] = equal[groups // 4 : groups // 2 : 3]
+        late = np.arange(groups // 2, groups, 2)
+        L[late] = equal[late]
+        L[late[::5], m // 2] = 1.0  # all but one
+        near = late[::3] + 1
+        near = near[near < groups]
+        L[near, 1] = (L[near, 0] + g[near, 0]) - g[near, 1]  # entries 0 and 1 tie, or nearly
+        L = L.reshape(rows, cols)
+        Wm_o, _, idx_o = oracle.mask_fwd(bf16_bits(W), L, n, m, 0.5, 1.0, seed, step, 0)
+        for soft in (False, True):
+            Wm, _, idx = roi.mask_fwd(W, torch.from_numpy(L).to(dev), n, m, 0.5, 1.0, seed, step,
+                                      0, want_soft=True, soft_forward=soft)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), idx_o), f"indices differ ({value}, {soft})"
+            if not soft:
+                assert np.array_equal(bf16_bits(Wm).reshape(-1), Wm_o), f"W_masked ({value})"
+
+
 # --------------------------------------------------------------------------- layout properties
 @pytest.mark.parametrize("tau", [1.0, 0.5, 0.4])
 def test_split_calls_equal_one_slab_call(dev, tau):
