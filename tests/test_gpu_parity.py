@@ -345,7 +345,9 @@ def test_logits_over_lambda(dev, n, m, lam):
     torch.cuda.synchronize()
     pick = lambda x: np.asarray(x).reshape(groups, m)[tame]
     assert_close(pick(f32(S)), pick(S_o), "soft mask")
-    assert_close(pick(f32(d)), pick(d_o), "grad_logits", scale_aware=lam < 1.0)
+    # relative to the largest gradient, which falls as 1 / lambda
+    r = assert_close(pick(f32(d)), pick(d_o), "grad_logits", scale_aware=True)
+    say(f"  grad_logits err/bound {r:.3f}, largest {np.abs(pick(d_o)).max():.3g}")
 
 
 WIDE_SORT = [(n, m) for m in (16, 32) for n in (1, 3, 4, m // 2 + 1, m - 1, m)]
