@@ -121,9 +121,9 @@ __device__ __forceinline__ void store_cat(float* p, const float (&a)[C])
 
 // Threads (and groups) per block of the kernels with one lane per group.
 constexpr int kCatBlock = 256;
-// Groups with at least 8 logits (32 bytes) are staged: read per lane from
-// global memory, their 32-280-byte strides would touch up to 8x more cache
-// lines per load instruction than a contiguous 16-byte-per-lane stream.
+// Groups of 8 logits (32 bytes; the largest that take these kernels) are staged:
+// read per lane from global memory, their stride would touch twice the cache
+// lines per load instruction of a contiguous 16-byte-per-lane stream.
 constexpr bool cat_staged(int C) { return C >= 8; }
 // The backward stages 6 candidates (2:4) as well: per lane, its 24-byte
 // strides leave every gradient store instruction covering only part of its

@@ -90,39 +90,37 @@ __global__ __launch_bounds__(kBlock) void export_kernel(ExportArgs a)
                 for (int j = 0; j < M; ++j) wm[j] = rank[j] < N ? w[j] : 0u;
                 store_group_bf16<M>(a.Wm + q * M, wm);
             }
-            {
-                // kept entries in increasing index order, in registers
-                uint32_t kv[N], ki[N];
+            // kept entries in increasing index order, in registers
+            uint32_t kv[N], ki[N];
 #pragma unroll
-                for (int p = 0; p < N; ++p) kv[p] = ki[p] = 0;
-                int pos = 0;
+            for (int p = 0; p < N; ++p) kv[p] = ki[p] = 0;
+            int pos = 0;
 #pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    const bool keep = rank[j] < N;
+            for (int j = 0; j < M; ++j) {
+                const bool keep = rank[j] < N;
 #pragma unroll
-                    for (int p = 0; p < N; ++p) {
-                        kv[p] = (keep && pos == p) ? w[j] : kv[p];
-                        ki[p] = (keep && pos == p) ? (uint32_t)j : ki[p];
-                    }
-                    pos += keep ? 1 : 0;
+                for (int p = 0; p < N; ++p) {
+                    kv[p] = (keep && pos == p) ? w[j] : kv[p];
+                    ki[p] = (keep && pos == p) ? (uint32_t)j : ki[p];
                 }
-                if (a.vals) {
-                    if constexpr (N % 2 == 0) {
-#pragma unroll
-                        for (int p = 0; p < N; p += 2)
-                            stream_store(kv[p] | (kv[p + 1] << 16),
-                                         reinterpret_cast<uint32_t*>(a.vals + q * N + p));
-                    } else {
-#pragma unroll
-                        for (int p = 0; p < N; ++p) a.vals[q * N + p] = (uint16_t)kv[p];
-                    }
-                }
-                if (a.idx) {
-#pragma unroll
-                    for (int p = 0; p < N; ++p) a.idx[q * N + p] = (uint8_t)ki[p];
-                }
-                if constexpr (M == 4 && N == 2) nib = ki[0] | (ki[1] << 2);
+                pos += keep ? 1 : 0;
             }
+            if (a.vals) {
+                if constexpr (N % 2 == 0) {
+#pragma unroll
+                    for (int p = 0; p < N; p += 2)
+                        stream_store(kv[p] | (kv[p + 1] << 16),
+                                     reinterpret_cast<uint32_t*>(a.vals + q * N + p));
+                } else {
+#pragma unroll
+                    for (int p = 0; p < N; ++p) a.vals[q * N + p] = (uint16_t)kv[p];
+                }
+            }
+            if (a.idx) {
+#pragma unroll
+                for (int p = 0; p < N; ++p) a.idx[q * N + p] = (uint8_t)ki[p];
+            }
+            if constexpr (M == 4 && N == 2) nib = ki[0] | (ki[1] << 2);
         }
         if constexpr (M == 4 && N == 2) {
             if (a.meta) { // uniform: the same for every lane
@@ -161,8 +159,8 @@ __device__ __forceinline__ int pick4(const int (&p)[4], int i)
     return i & 2 ? b : a;
 }
 
-// Copies `bytes` of LDS to a 16-byte aligned place; `unit` bytes at a time past
-// the last 16.
+// Copies `count` entries from LDS to a 16-byte aligned place, 16 bytes per
+// thread, and one entry per thread past the last whole 16 bytes.
 template <typename T>
 __device__ __forceinline__ void copy_out(const T* lds, T* dst, int count)
 {

@@ -275,11 +275,13 @@ __device__ __forceinline__ bool fast_keys_separated(const float (&k)[M])
 // phi / lambda, correctly rounded, for the logits of a lane.  div_y is 1 /
 // lambda where quotient() may use it, else 0 (quotient_reciprocal, the host's
 // choice).  A wave with a logit too large for it (an infinity, or a mask's
-// lowest value) divides; the same bits either way.  Five fused operations and
-// a share of the maximum, 16 issue cycles a logit, against 38 for the IEEE
-// sequence.  Backwards over 6e8 weights on MI355X at lambda = 0.316, with the
-// division and so: 2:4 at tau = 0.5 1.52 and 1.45 ms, 4:8 2.21 and 2.10 ms, 8:16
-// 2.47 and 2.36 ms.
+// lowest value) divides.  The keys are the same either way: the last bit may
+// differ only of a quotient below 2^-80, which vanishes beside the noise, at
+// least 2^-22 in magnitude for all but one of its 2^23 values (which is 0).
+// Five fused operations and a share of the maximum, 16 issue cycles a logit,
+// against 38 for the IEEE sequence.  Backwards over 6e8 weights on MI355X at
+// lambda = 0.316, with the division and so: 2:4 at tau = 0.5 1.52 and 1.45 ms,
+// 4:8 2.21 and 2.10 ms, 8:16 2.47 and 2.36 ms.
 template <int K>
 __device__ __forceinline__ void quotients(const float (&phi)[K], float lambda, float div_y,
                                           float (&a)[K])

@@ -232,7 +232,7 @@ __device__ __forceinline__ float float_of_sortable_int(int v)
 template <int M>
 __device__ __forceinline__ void sort_group(int (&p)[4], int part)
 {
-    static_assert(M == 8 || M == 16 || M == 32, "group size");
+    static_assert(M == 16 || M == 32, "group size");
     constexpr int kMax = 0x7FFFFFFF, kMin = -0x7FFFFFFF - 1;
     const int b1 = (part & 1) == 0 ? kMax : kMin;
     const int b2 = (part & 2) == 0 ? kMax : kMin;

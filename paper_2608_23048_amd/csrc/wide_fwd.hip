@@ -20,8 +20,7 @@ namespace {
 template <bool kRelax>
 constexpr int kWideFwdSlots = kRelax ? 1 : ROI_WIDE_FWD_SLOTS;
 
-// The hard mask of one slot, stored: W where kept, and the indices of the
-// lane's ranks 4 part .. 4 part + 3.
+// The hard mask of one slot, stored: W where kept.
 template <int N>
 __device__ __forceinline__ void store_wide_mask(const FwdPiece& pc, int64_t slot, u32x2 wv,
                                                 const bool (&keep)[4])
@@ -32,6 +31,7 @@ __device__ __forceinline__ void store_wide_mask(const FwdPiece& pc, int64_t slot
     stream_store(out, reinterpret_cast<u32x2*>(pc.Wm + slot * 4));
 }
 
+// The indices of the lane's ranks 4 part .. 4 part + 3.
 template <int L, int N>
 __device__ __forceinline__ void store_wide_idx(const FwdPiece& pc, int64_t slot, int part,
                                                const int (&sidx)[4])
