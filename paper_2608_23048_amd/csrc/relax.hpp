@@ -110,15 +110,6 @@ struct StepRec {
     float om[M]; // 1 - mu^(k), evaluated as the sum of the other entries over the total
 };
 
-template <int M>
-__device__ __forceinline__ float largest(const float (&x)[M])
-{
-    float mx = x[0];
-#pragma unroll
-    for (int j = 1; j < M; ++j) mx = fmaxf(mx, x[j]);
-    return mx;
-}
-
 // Keys scaled for the relaxation: b_j = kappa_j * key_scale, the softmax
 // argument alpha / tau in log2 units; bmax = max b.  Returns the span
 // (max - min) of b.  key_scale is log2(e) / tau for keys in natural units and
@@ -143,42 +134,6 @@ __device__ __forceinline__ float scaled_keys(const float (&kappa)[M], float key_
     return kSpan ? (kmax - kmin) * key_scale : 0.0f;
 }
 
-// The first step's exponentials, exp2((kappa_j - kmax) key_scale).  The fused
-// form shifts by bmax, the rounded kmax key_scale; its rounding, up to ulp(bmax)
-// / 2, is at most 1 up to kFusedShiftMax.  Keys of 1e10 that tie (a mask's value
-// in a whole group) would overflow, so beyond it the keys are shifted before
-// they are scaled: exactly, where they are close.  The branch is the wave's:
-// waves without such a group pay one comparison, and no selects.  Both forms of
-// the recursion start from them, so a wave with groups of both computes them
-// once (soft forwards with a mask's lowest value in a tenth of the entries,
-// 46.8e6 weights on MI355X, with exponentials of each form's own and so: 4:8 110
-// and 105 us, 8:16 196 and 191 us, 1:4 67 and 65 us).
-constexpr float kFusedShiftMax = 0x1p24f;
-
-template <int K, typename Max>
-__device__ __forceinline__ void first_exps(const float (&kappa)[K], float key_scale, float bmax,
-                                           Max group_kmax, float (&e)[K])
-{
-#pragma unroll
-    for (int j = 0; j < K; ++j) e[j] = __builtin_fmaf(kappa[j], key_scale, -bmax);
-    if (__any(fabsf(bmax) > kFusedShiftMax)) {
-        const bool huge = fabsf(bmax) > kFusedShiftMax;
-        const float kmax = group_kmax();
-#pragma unroll
-        for (int j = 0; j < K; ++j) e[j] = huge ? (kappa[j] - kmax) * key_scale : e[j];
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) e[j] = __builtin_amdgcn_exp2f(e[j]);
-}
-
-// The same from the scaled keys, for the kernels without the exp-domain form.
-template <int K>
-__device__ __forceinline__ void shifted_exps(const float (&b)[K], float bmax, float (&e)[K])
-{
-#pragma unroll
-    for (int j = 0; j < K; ++j) e[j] = __builtin_amdgcn_exp2f(b[j] - bmax);
-}
-
 // Relaxation (§3.2 recursion, Algorithm 1) in fp32:
 //   alpha^(1) = kappa; mu^(k) = softmax(alpha^(k) / tau);
 //   alpha^(k+1) = alpha^(k) + log(1 - mu^(k));  S = sum_k mu^(k).
@@ -188,10 +143,9 @@ __device__ __forceinline__ void shifted_exps(const float (&b)[K], float bmax, fl
 // (sum of the other exponentials) / total, which never cancels, and
 // log(1 - mu) is floored at log(FLT_MIN).  The records of the updating steps
 // hold max(1 - mu, FLT_MIN), the value whose log was taken: a floored entry
-// shows as exactly FLT_MIN (relax_backward).  e0: the first step's exponentials
-// (first_exps, or shifted_exps where the exp-domain form is off).
+// shows as exactly FLT_MIN (relax_backward).
 template <int M, int N, bool kWantS, bool kKeep>
-__device__ __forceinline__ void relax_forward(float (&b)[M], const float (&e0)[M], float inv_tau,
+__device__ __forceinline__ void relax_forward(float (&b)[M], float bmax0, float inv_tau,
                                               float (&S)[M], StepRec<M> (&rec)[N])
 {
 #pragma unroll
@@ -200,9 +154,9 @@ __device__ __forceinline__ void relax_forward(float (&b)[M], const float (&e0)[M
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         float e[M];
-        if (k == 0) {
+        if (k == 0) { // the largest b is known
 #pragma unroll
-            for (int j = 0; j < M; ++j) e[j] = e0[j];
+            for (int j = 0; j < M; ++j) e[j] = __builtin_amdgcn_exp2f(b[j] - bmax0);
         } else {
             float bmax = b[0];
 #pragma unroll
@@ -256,6 +210,30 @@ __device__ __forceinline__ void relax_forward(float (&b)[M], const float (&e0)[M
 constexpr float kExpNormalBound = 91.0f;
 constexpr float kExpSpanAccuracy = 32.0f;
 
+// The first step's exponentials, exp2((kappa_j - kmax) key_scale).  The fused
+// form shifts by bmax, the rounded kmax key_scale; its rounding, up to ulp(bmax)
+// / 2, is at most 1 up to kFusedShiftMax.  Keys of 1e10 that tie (a mask's value
+// in a whole group) would overflow, so beyond it the keys are shifted before
+// they are scaled: exactly, where they are close.  The branch is the wave's:
+// waves without such a group pay one comparison, and no selects.
+constexpr float kFusedShiftMax = 0x1p24f;
+
+template <int K, typename Max>
+__device__ __forceinline__ void first_exps(const float (&kappa)[K], float key_scale, float bmax,
+                                           Max group_kmax, float (&e)[K])
+{
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        e[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(kappa[j], key_scale, -bmax));
+    if (__any(fabsf(bmax) > kFusedShiftMax)) {
+        const bool huge = fabsf(bmax) > kFusedShiftMax;
+        const float kmax = group_kmax();
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            e[j] = huge ? __builtin_amdgcn_exp2f((kappa[j] - kmax) * key_scale) : e[j];
+    }
+}
+
 template <int kQ>
 __device__ __forceinline__ float pow_q(float om, float q)
 {
@@ -265,16 +243,22 @@ __device__ __forceinline__ float pow_q(float om, float q)
 }
 
 template <int M, int N, bool kWantS, bool kKeep, int kQ>
-__device__ __forceinline__ void relax_forward_exp(const float (&e0)[M], float q, float (&S)[M],
+__device__ __forceinline__ void relax_forward_exp(const float (&kappa)[M], float key_scale,
+                                                  float bmax, float q, float (&S)[M],
                                                   StepRec<M> (&rec)[N])
 {
     static_assert(kQ >= 0 && kQ <= 2, "exp-domain recursion: kQ");
     float e[M];
+    const auto largest = [&] {
+        float kmax = kappa[0];
 #pragma unroll
-    for (int j = 0; j < M; ++j) {
-        e[j] = e0[j];
+        for (int j = 1; j < M; ++j) kmax = fmaxf(kmax, kappa[j]);
+        return kmax;
+    };
+    first_exps<M>(kappa, key_scale, bmax, largest, e);
+#pragma unroll
+    for (int j = 0; j < M; ++j)
         if (kWantS) S[j] = 0.0f;
-    }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         float others[M], total;

@@ -420,14 +420,14 @@ __global__ __launch_bounds__(kLaneBlock) void fwd_lane_kernel(FwdBatch a)
                 if (kWantIdx) store_idx<M, N>(pc.idx + q * N, rank);
             }
             if (kRelax) {
-                float S[M], b[M], e0[M], bmax;
+                float S[M], b[M], bmax;
                 StepRec<M> unused[N]; // not written when records are not kept
                 const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-                first_exps<M>(kappa, a.key_scale, bmax, [&] { return largest<M>(kappa); }, e0);
                 if (span <= a.exp_span)
-                    relax_forward_exp<M, N, true, false, kQ>(e0, a.inv_tau, S, unused);
+                    relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
+                                                     unused);
                 else
-                    relax_forward<M, N, true, false>(b, e0, a.inv_tau, S, unused);
+                    relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
                 if (pc.S) {
                     f32x4* s4 = reinterpret_cast<f32x4*>(pc.S + q * M);
 #pragma unroll
@@ -501,19 +501,16 @@ __device__ __forceinline__ void soft_lane_chunk(const FwdBatch& a, const FwdPiec
         if (!kFull && q >= ng_total) continue;
         float kappa[M];
         keys_from_noise<M>(phi[u], ng[u], a.lambda, a.div_y, kappa);
-        float S[M], b[M], e0[M], bmax;
+        float S[M], b[M], bmax;
         StepRec<M> unused[N]; // not written when records are not kept
         if constexpr (kQ < 0) {
             scaled_keys<M, false>(kappa, a.key_scale, b, bmax);
-            shifted_exps<M>(b, bmax, e0);
-            relax_forward<M, N, true, false>(b, e0, a.inv_tau, S, unused);
+            relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
+        } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
+            relax_forward_exp<M, N, true, false, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S,
+                                                     unused);
         } else {
-            const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-            first_exps<M>(kappa, a.key_scale, bmax, [&] { return largest<M>(kappa); }, e0);
-            if (span <= a.exp_span)
-                relax_forward_exp<M, N, true, false, kQ>(e0, a.inv_tau, S, unused);
-            else
-                relax_forward<M, N, true, false>(b, e0, a.inv_tau, S, unused);
+            relax_forward<M, N, true, false>(b, bmax, a.inv_tau, S, unused);
         }
         store_soft_product<M>(pc.Wm + q * M, w[u], S);
     }
@@ -568,22 +565,18 @@ __device__ __forceinline__ void bwd_group4(const BwdBatch& a, const BwdPiece& pc
     // log(1 - mu) is then out of reach), else the log-domain one with the
     // floor's case in the sweep (relax.hpp).
     StepRec<M> rec[N];
-    float S_unused[M], b[M], e0[M], abar[M], bmax;
+    float S_unused[M], b[M], abar[M], bmax;
     if constexpr (kQ < 0) { // the exp-domain form is off at this temperature
         scaled_keys<M, false>(kappa, a.key_scale, b, bmax);
-        shifted_exps<M>(b, bmax, e0);
-        relax_forward<M, N, false, true>(b, e0, a.inv_tau, S_unused, rec);
+        relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
         relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
+    } else if (scaled_keys<M>(kappa, a.key_scale, b, bmax) <= a.exp_span) {
+        relax_forward_exp<M, N, false, true, kQ>(kappa, a.key_scale, bmax, a.inv_tau, S_unused,
+                                                  rec);
+        relax_backward<M, N, kQ == 1, false>(rec, sbar, a.inv_tau, abar);
     } else {
-        const float span = scaled_keys<M>(kappa, a.key_scale, b, bmax);
-        first_exps<M>(kappa, a.key_scale, bmax, [&] { return largest<M>(kappa); }, e0);
-        if (span <= a.exp_span) {
-            relax_forward_exp<M, N, false, true, kQ>(e0, a.inv_tau, S_unused, rec);
-            relax_backward<M, N, kQ == 1, false>(rec, sbar, a.inv_tau, abar);
-        } else {
-            relax_forward<M, N, false, true>(b, e0, a.inv_tau, S_unused, rec);
-            relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
-        }
+        relax_forward<M, N, false, true>(b, bmax, a.inv_tau, S_unused, rec);
+        relax_backward<M, N, false, true>(rec, sbar, a.inv_tau, abar);
     }
     float grad[M]; // dL/dphi = dL/dkappa / lambda
 #pragma unroll

@@ -383,12 +383,9 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
     }
     // kQ < 0: the exp-domain form is off at this temperature (no span needed)
     const float span = kQ < 0 ? 0.0f : (kmax - group_min<L>(min4(kappa))) * c;
-    float ex[4]; // the first step's exponentials, in both forms
-    if constexpr (kQ < 0)
-        shifted_exps<4>(b, bmax0, ex);
-    else
-        first_exps<4>(kappa, c, bmax0, [&] { return group_max<L>(max4(kappa)); }, ex);
     if (kQ >= 0 && span <= exp_span) { // the same on all lanes of the group
+        float ex[4];
+        first_exps<4>(kappa, c, bmax0, [&] { return group_max<L>(max4(kappa)); }, ex);
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             float others[4], t;
@@ -412,7 +409,10 @@ __device__ __forceinline__ bool wide_relax_forward(const float (&kappa)[4], floa
     }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        if (k > 0) shifted_exps<4>(b, group_max<L>(max4(b)), ex);
+        float ex[4];
+        const float bmax = k == 0 ? bmax0 : group_max<L>(max4(b));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ex[e] = __builtin_amdgcn_exp2f(b[e] - bmax);
         float others[4], t;
         sums_but_one<4>(ex, others, t);
         const float ext = sum_other_lanes<L>(t);
