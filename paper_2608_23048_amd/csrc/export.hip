@@ -213,44 +213,42 @@ __global__ __launch_bounds__(kBlock) void export_wide_kernel(ExportArgs a)
             nib = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) nib |= own[e] >= kth ? 1u << e : 0u;
-            if (__any(tied)) {
+            if (__any(tied || !(sum == sum))) { // rare
+                // Hidden, so that nothing of this is computed ahead of the branch.
+                int at = part, top = kth;
+                asm volatile("" : "+v"(at), "+v"(top));
                 uint32_t above = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) above |= own[e] > kth ? 1u << e : 0u;
-                const int room = n - __popc(group_or<L>(above << (4 * part)));
-                const uint32_t equal = group_or<L>((nib ^ above) << (4 * part));
+                for (int e = 0; e < 4; ++e) above |= own[e] > top ? 1u << e : 0u;
+                const int room = n - __popc(group_or<L>(above << (4 * at)));
+                const uint32_t equal = group_or<L>((nib ^ above) << (4 * at));
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const uint32_t before = equal & ((1u << (4 * part + e)) - 1u);
+                    const uint32_t before = equal & ((1u << (4 * at + e)) - 1u);
                     if (__popc(before) >= room) nib &= ~(1u << e) | above;
                 }
-            }
-            // the sum is NaN for opposite infinities too: look again, at each logit
-            if (__any(!(sum == sum)) &&
-                __any(phi[0] != phi[0] || phi[1] != phi[1] || phi[2] != phi[2] ||
-                      phi[3] != phi[3])) {
-                // Kept out of the common path's way: a rolled loop, its lane number
-                // hidden so that nothing of it is computed ahead of the branch.
-                int at = part;
-                asm volatile("" : "+v"(at));
-                int rank[4] = {0, 0, 0, 0};
+                // the sum is NaN for opposite infinities too: look at each logit
+                if (__any(phi[0] != phi[0] || phi[1] != phi[1] || phi[2] != phi[2] ||
+                          phi[3] != phi[3])) {
+                    int rank[4] = {0, 0, 0, 0};
 #pragma unroll 1
-                for (int t = 0; t < L; ++t) {
+                    for (int t = 0; t < L; ++t) {
 #pragma unroll
-                    for (int f = 0; f < 4; ++f) {
-                        const float v = __shfl(phi[f], first + t);
+                        for (int f = 0; f < 4; ++f) {
+                            const float v = __shfl(phi[f], first + t);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int i = 4 * t + f, j = 4 * at + e;
-                            // the earlier of two entries wins when it is >= the later
-                            if (i < j) rank[e] += v >= phi[e] ? 1 : 0;
-                            if (i > j) rank[e] += phi[e] >= v ? 0 : 1;
+                            for (int e = 0; e < 4; ++e) {
+                                const int i = 4 * t + f, j = 4 * at + e;
+                                // the earlier of two entries wins when it is >= the later
+                                if (i < j) rank[e] += v >= phi[e] ? 1 : 0;
+                                if (i > j) rank[e] += phi[e] >= v ? 0 : 1;
+                            }
                         }
                     }
-                }
-                nib = 0;
+                    nib = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) nib |= rank[e] < n ? 1u << e : 0u;
+                    for (int e = 0; e < 4; ++e) nib |= rank[e] < n ? 1u << e : 0u;
+                }
             }
         }
         const uint32_t kept = group_or<L>(nib << (4 * part));
