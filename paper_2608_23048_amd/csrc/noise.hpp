@@ -280,8 +280,8 @@ __device__ __forceinline__ bool fast_keys_separated(const float (&k)[M])
 // least 2^-22 in magnitude for all but one of its 2^23 values (which is 0).
 // Five fused operations and a share of the maximum, 16 issue cycles a logit,
 // against 38 for the IEEE sequence.  Backwards over 6e8 weights on MI355X at
-// lambda = 0.316, with the division and so: 2:4 at tau = 0.5 1.52 and 1.45 ms,
-// 4:8 2.21 and 2.10 ms, 8:16 2.47 and 2.36 ms.
+// lambda = 0.316 and tau = 0.5, with the division and so: 2:4 1.57 and 1.53 ms,
+// 4:8 2.23 and 2.12 ms, 8:16 3.99 and 3.87 ms.
 template <int K>
 __device__ __forceinline__ void quotients(const float (&phi)[K], float lambda, float div_y,
                                           float (&a)[K])
